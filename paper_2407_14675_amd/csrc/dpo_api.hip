@@ -33,8 +33,12 @@ struct dpo_ctx {
   int64_t N = 0, n_free = 0;
   uint8_t* kind = nullptr;
   uint32_t* free_node = nullptr;  // packed coordinates of the free nodes, node order
+  uint32_t* sweep_node = nullptr;  // the free list in the factorised sweeps' order (see SweepArgs)
+  uint16_t* sweep_pos = nullptr;
+  int* one_cell = nullptr;
   double* rinv = nullptr;         // 1/r per r node (FP64)
   float* gtab = nullptr;          // [2][n_m]: thrust displacement per unit sin (v_r) / cos (v_t)
+  char* node_tab = nullptr;       // tables of the node terms (see SweepArgs)
   double c0 = 0, c1 = 0, c2 = 0;  // dt/h for r, v_r, v_t
   float gm = 0;                   // thrust displacement along m
   bool fast_ok = false;           // the factorised thrust kernel applies
@@ -227,6 +231,28 @@ Grid make_grid(const dpo_grid& g, bool periodic3 = false) {
   return G;
 }
 
+// Constants of scan_window for a table of K angles, the first rounded up.
+float scan_y0_for(int K) { return std::nextafterf((float)(1.0 - std::cos(3.14159265358979323846 / K)), 4.0f); }
+float scan_k_for(int K) { return (float)(K / (2.0 * 3.14159265358979323846)); }
+
+// The node-term tables lie one after another in one allocation, the widest
+// entries first; returns its size in bytes.
+size_t node_table_pointers(const dpo_ctx* c, SweepArgs& a) {
+  const int32_t* n = c->grid.n;
+  char* p = c->node_tab;
+  auto take = [&](size_t bytes) {
+    char* q = p;
+    p += bytes;
+    return q;
+  };
+  a.mrow = reinterpret_cast<const float4*>(take(sizeof(float4) * n[3]));
+  a.drift2 = reinterpret_cast<const double*>(take(sizeof(double) * n[1] * n[2]));
+  a.drift1 = reinterpret_cast<const float*>(take(sizeof(float) * n[0] * n[2]));
+  a.drift0 = reinterpret_cast<const float*>(take(sizeof(float) * n[1]));
+  a.drift3 = c->P.model == DPO_MODEL_CROWN ? reinterpret_cast<const float*>(take(sizeof(float) * n[0] * n[2])) : nullptr;
+  return (size_t)(p - c->node_tab);
+}
+
 SweepArgs base_args(const dpo_ctx* c) {
   SweepArgs a;
   std::memset(&a, 0, sizeof(a));
@@ -234,9 +260,11 @@ SweepArgs base_args(const dpo_ctx* c) {
   a.P = c->P;
   a.free_node = c->free_node;
   a.n_free = (int)c->n_free;
+  a.sweep_node = c->sweep_node;
+  a.sweep_pos = c->sweep_pos;
+  a.one_cell = c->one_cell;
   a.rinv = c->rinv;
-  a.g1tab = c->gtab;
-  a.g2tab = c->gtab + c->grid.n[3];
+  node_table_pointers(c, a);
   a.c0 = c->c0;
   a.c1 = c->c1;
   a.c2 = c->c2;
@@ -251,6 +279,8 @@ SweepArgs base_args(const dpo_ctx* c) {
   a.rot_scan = c->rot;
   a.rot_local = c->rot + kRot;
   a.half_width = (float)(2.0 * 3.14159265358979323846 / (double)(c->search.n_scan > 0 ? c->search.n_scan : 1));
+  a.scan_y0 = scan_y0_for(c->n_ang);
+  a.scan_k = scan_k_for(c->n_ang);
   a.n_local = c->search.n_local;
   a.local_half_width = (float)c->search.local_half_width;
   a.fallback_tol = (float)c->search.fallback_tol;
@@ -980,6 +1010,25 @@ int dpo_create(const dpo_grid* grid, const dpo_problem* prob, const dpo_search* 
     return cleanup(DPO_ENOMEM);
   }
   if ((rc = upload_table(c)) != DPO_OK) return cleanup(rc);
+  {
+    SweepArgs a;
+    const size_t bytes = node_table_pointers(c, a), n = (size_t)std::max(1, total);
+    if (hipMalloc(&c->node_tab, bytes) != hipSuccess ||
+        (c->fast_ok && (hipMalloc(&c->sweep_node, sizeof(uint32_t) * n) != hipSuccess ||
+                        hipMalloc(&c->sweep_pos, sizeof(uint16_t) * n) != hipSuccess ||
+                        hipMalloc(&c->one_cell, sizeof(int) * blocks_for(n, kOrderChunk)) != hipSuccess))) {
+      c->err = "device allocation failed in dpo_create";
+      return cleanup(DPO_ENOMEM);
+    }
+    a = base_args(c);
+    e = launch_node_tables(a, c->gtab, c->gtab + grid->n[3], nullptr);
+    if (e == hipSuccess && c->fast_ok && total > 0) e = launch_order_free(a, c->sweep_node, c->sweep_pos, c->one_cell, nullptr);
+    if (e == hipSuccess) e = hipDeviceSynchronize();
+    if (e != hipSuccess) {
+      c->err = std::string("dpo_create: ") + hipGetErrorString(e);
+      return cleanup(DPO_EHIP);
+    }
+  }
   *out = c;
   return cleanup(DPO_OK);
 }
@@ -991,6 +1040,10 @@ void dpo_destroy(dpo_ctx* c) {
   if (c->free_node) hipFree(c->free_node);
   if (c->rinv) hipFree(c->rinv);
   if (c->gtab) hipFree(c->gtab);
+  if (c->sweep_node) hipFree(c->sweep_node);
+  if (c->sweep_pos) hipFree(c->sweep_pos);
+  if (c->one_cell) hipFree(c->one_cell);
+  if (c->node_tab) hipFree(c->node_tab);
   if (c->tab) hipFree(c->tab);
   if (c->rot) hipFree(c->rot);
   if (c->partial) hipFree(c->partial);
@@ -1680,9 +1733,8 @@ dpo::CtxView dpo::ctx_view(const dpo_ctx* c) {
 }
 
 // ============================================================ batched solve
-// The batch keeps every per-problem array in one concatenated device
-// allocation (values A and B, policy, free-node lists, 1/r and thrust
-// tables) and a pointer-free record per problem with its offsets.
+// The batch keeps the problems' values (A and B) and policies in one
+// concatenated device allocation each, the rest in the problems' own contexts.
 struct dpo_batch {
   int n = 0;
   std::vector<dpo_ctx*> ctx;
@@ -1690,16 +1742,11 @@ struct dpo_batch {
   int mode = 0;
   hipStream_t stream = nullptr;
   std::vector<long long> v_off;  // node offsets (n + 1)
-  std::vector<int> free_off;     // free-list offsets (n + 1)
   float* Va = nullptr;
   float* Vb = nullptr;
   float* ang = nullptr;
   uint8_t* thr = nullptr;
-  uint32_t* free_all = nullptr;
-  double* rinv_all = nullptr;
-  float* g_all = nullptr;
-  std::vector<BatchProblem> rec;  // host copy of the records (tile_begin per config)
-  BatchProblem* d_probs = nullptr;  // records of the running problems, in run order (n)
+  SweepArgs* d_sweeps = nullptr;  // sweep arguments of the running problems, in run order: A -> B, then B -> A (2 n)
   int* d_tile_begin = nullptr;  // over the running problems (n + 1)
   int* d_tile_run = nullptr;    // running problem of each tile (partial_cap)
   int* d_run = nullptr;         // running problems (n)
@@ -1725,51 +1772,48 @@ int bfail(dpo_batch* b, int code, const std::string& msg) {
     if (e_ != hipSuccess) return bfail((b), DPO_EHIP, std::string(#call) + ": " + hipGetErrorString(e_)); \
   } while (0)
 
-// Tile table over the running problems for workgroup size `block` (records
-// uploaded too); returns the tile count.
-int batch_tables(dpo_batch* b, int block, const std::vector<int>& run, int* n_tiles) {
-  std::vector<int> tb(run.size() + 1, 0);
-  std::vector<BatchProblem> rr(run.size());
-  for (size_t k = 0; k < run.size(); k++) {
-    b->rec[run[k]].tile_begin = tb[k];
-    rr[k] = b->rec[run[k]];
-    tb[k + 1] = tb[k] + blocks_for(b->ctx[run[k]]->n_free, block);
+// Tile table over the running problems for workgroups of `block` threads, and
+// their sweep arguments for both directions of the value buffers (uploaded);
+// returns the tile count.
+int batch_tables(dpo_batch* b, int block, const std::vector<int>& run, bool policy, int* n_tiles) {
+  const size_t n = run.size();
+  std::vector<int> tb(n + 1, 0);
+  std::vector<SweepArgs> rec(2 * n);
+  for (size_t k = 0; k < n; k++) {
+    const dpo_ctx* c = b->ctx[run[k]];
+    const long long off = b->v_off[run[k]];
+    SweepArgs a = base_args(c);
+    a.pol_ang = policy ? b->ang + off : nullptr;
+    a.pol_thr = policy ? b->thr + off : nullptr;
+    for (int parity = 0; parity < 2; parity++) {
+      a.V_in = (parity ? b->Vb : b->Va) + off;
+      a.V_out = (parity ? b->Va : b->Vb) + off;
+      rec[parity * n + k] = a;
+    }
+    tb[k + 1] = tb[k] + blocks_for(c->n_free, block);
   }
-  if (tb[run.size()] > b->partial_cap) return bfail(b, DPO_EINVAL, "batch: too many tiles for the partial buffer");
-  std::vector<int> tr(std::max(1, tb[run.size()]));
-  for (size_t k = 0; k < run.size(); k++)
-    std::fill(tr.begin() + tb[k], tr.begin() + tb[k + 1], (int)k);
-  BHIP_TRY(b, hipMemcpyAsync(b->d_probs, rr.data(), sizeof(BatchProblem) * rr.size(), hipMemcpyHostToDevice, b->stream));
-  BHIP_TRY(b, hipMemcpyAsync(b->d_run, run.data(), sizeof(int) * run.size(), hipMemcpyHostToDevice, b->stream));
+  if (tb[n] > b->partial_cap) return bfail(b, DPO_EINVAL, "batch: too many tiles for the partial buffer");
+  std::vector<int> tr(std::max(1, tb[n]));
+  for (size_t k = 0; k < n; k++) std::fill(tr.begin() + tb[k], tr.begin() + tb[k + 1], (int)k);
+  BHIP_TRY(b, hipMemcpyAsync(b->d_sweeps, rec.data(), sizeof(SweepArgs) * rec.size(), hipMemcpyHostToDevice, b->stream));
+  BHIP_TRY(b, hipMemcpyAsync(b->d_run, run.data(), sizeof(int) * n, hipMemcpyHostToDevice, b->stream));
   BHIP_TRY(b, hipMemcpyAsync(b->d_tile_begin, tb.data(), sizeof(int) * tb.size(), hipMemcpyHostToDevice, b->stream));
-  BHIP_TRY(b, hipMemcpyAsync(b->d_tile_run, tr.data(), sizeof(int) * tb[run.size()], hipMemcpyHostToDevice, b->stream));
+  BHIP_TRY(b, hipMemcpyAsync(b->d_tile_run, tr.data(), sizeof(int) * tb[n], hipMemcpyHostToDevice, b->stream));
   BHIP_TRY(b, hipStreamSynchronize(b->stream));
-  *n_tiles = tb[run.size()];
+  *n_tiles = tb[n];
   return DPO_OK;
 }
 
-BatchArgs batch_args(dpo_batch* b, double tol, int n_run, int n_tiles, bool policy) {
+BatchArgs batch_args(dpo_batch* b, double tol, const std::vector<int>& run, int n_tiles) {
   BatchArgs a;
   std::memset(&a, 0, sizeof(a));
-  const dpo_ctx* c0 = b->ctx[0];
-  a.probs = b->d_probs;
+  a.sweeps = b->d_sweeps;
   a.run = b->d_run;
   a.tile_begin = b->d_tile_begin;
   a.tile_run = b->d_tile_run;
-  a.n_run = n_run;
+  a.n_run = (int)run.size();
   a.n_tiles = n_tiles;
-  a.free_all = b->free_all;
-  a.rinv_all = b->rinv_all;
-  a.g_all = b->g_all;
-  a.Va = b->Va;
-  a.Vb = b->Vb;
-  a.ang_all = policy ? b->ang : nullptr;
-  a.thr_all = policy ? b->thr : nullptr;
-  a.tab = c0->tab;
-  a.n_ang = c0->n_ang;
-  a.n_golden = c0->search.n_golden;
-  a.half_width = (float)(2.0 * 3.14159265358979323846 / (double)(c0->search.n_scan > 0 ? c0->search.n_scan : 1));
-  a.rot_scan = c0->rot;
+  a.n_ang = b->ctx[0]->n_ang;
   a.done = b->d_done;
   a.partial = b->d_partial;
   a.resid = b->d_resid;
@@ -1813,8 +1857,8 @@ int batch_run(dpo_batch* b, double tol, int64_t max_sweeps, int S, int block, bo
   while (t < max_sweeps && !run.empty()) {
     if (!exec) {
       int n_tiles = 0;
-      if ((rc = batch_tables(b, block, run, &n_tiles)) != DPO_OK) break;
-      if ((rc = batch_graph(b, batch_args(b, tol, (int)run.size(), n_tiles, policy), block, S, &exec)) != DPO_OK) break;
+      if ((rc = batch_tables(b, block, run, policy, &n_tiles)) != DPO_OK) break;
+      if ((rc = batch_graph(b, batch_args(b, tol, run, n_tiles), block, S, &exec)) != DPO_OK) break;
     }
     hipError_t e = hipGraphLaunch(exec, b->stream);
     if (e == hipSuccess) e = hipMemcpyAsync(done.data(), b->d_done, sizeof(int) * n, hipMemcpyDeviceToHost, b->stream);
@@ -1880,8 +1924,6 @@ int dpo_batch_create(int32_t n_prob, const dpo_grid* grids, const dpo_problem* p
     return code;
   };
   b->v_off.assign(n_prob + 1, 0);
-  b->free_off.assign(n_prob + 1, 0);
-  std::vector<int> r_off(n_prob + 1, 0), g_off(n_prob + 1, 0);
   long long tiles64 = 0;
   for (int p = 0; p < n_prob; p++) {
     dpo_ctx* c = nullptr;
@@ -1896,23 +1938,17 @@ int dpo_batch_create(int32_t n_prob, const dpo_grid* grids, const dpo_problem* p
       return bail(DPO_EINVAL);
     }
     b->v_off[p + 1] = b->v_off[p] + c->N;
-    b->free_off[p + 1] = b->free_off[p] + (int)c->n_free;
-    r_off[p + 1] = r_off[p] + grids[p].n[0];
-    g_off[p + 1] = g_off[p] + 2 * grids[p].n[3];
     tiles64 += blocks_for(c->n_free, 64);
   }
   const long long NT = b->v_off[n_prob];
-  if (NT > 0x7fffffffLL || b->free_off[n_prob] < 0) {
+  if (NT > 0x7fffffffLL) {
     b->err = "batch: more than 2^31 nodes in total";
     return bail(DPO_EINVAL);
   }
   b->partial_cap = (int)std::max(1LL, tiles64);
   if (hipMalloc(&b->Va, sizeof(float) * NT) != hipSuccess || hipMalloc(&b->Vb, sizeof(float) * NT) != hipSuccess ||
       hipMalloc(&b->ang, sizeof(float) * NT) != hipSuccess || hipMalloc(&b->thr, (size_t)NT) != hipSuccess ||
-      hipMalloc(&b->free_all, sizeof(uint32_t) * std::max(1, b->free_off[n_prob])) != hipSuccess ||
-      hipMalloc(&b->rinv_all, sizeof(double) * r_off[n_prob]) != hipSuccess ||
-      hipMalloc(&b->g_all, sizeof(float) * g_off[n_prob]) != hipSuccess ||
-      hipMalloc(&b->d_probs, sizeof(BatchProblem) * n_prob) != hipSuccess ||
+      hipMalloc(&b->d_sweeps, sizeof(SweepArgs) * 2 * n_prob) != hipSuccess ||
       hipMalloc(&b->d_tile_begin, sizeof(int) * (n_prob + 1)) != hipSuccess ||
       hipMalloc(&b->d_tile_run, sizeof(int) * b->partial_cap) != hipSuccess ||
       hipMalloc(&b->d_run, sizeof(int) * n_prob) != hipSuccess ||
@@ -1921,30 +1957,6 @@ int dpo_batch_create(int32_t n_prob, const dpo_grid* grids, const dpo_problem* p
       hipMalloc(&b->d_resid, sizeof(double) * kPartial * n_prob) != hipSuccess) {
     b->err = "batch: device allocation failed";
     return bail(DPO_ENOMEM);
-  }
-  b->rec.resize(n_prob);
-  for (int p = 0; p < n_prob; p++) {
-    dpo_ctx* c = b->ctx[p];
-    hipError_t e = hipMemcpy(b->free_all + b->free_off[p], c->free_node, sizeof(uint32_t) * c->n_free, hipMemcpyDeviceToDevice);
-    if (e == hipSuccess) e = hipMemcpy(b->rinv_all + r_off[p], c->rinv, sizeof(double) * grids[p].n[0], hipMemcpyDeviceToDevice);
-    if (e == hipSuccess) e = hipMemcpy(b->g_all + g_off[p], c->gtab, sizeof(float) * 2 * grids[p].n[3], hipMemcpyDeviceToDevice);
-    if (e != hipSuccess) {
-      b->err = "batch: table copy failed";
-      return bail(DPO_EHIP);
-    }
-    BatchProblem& R = b->rec[p];
-    std::memset(&R, 0, sizeof(R));
-    R.G = c->G;
-    R.P = c->P;
-    R.c0 = c->c0;
-    R.c1 = c->c1;
-    R.c2 = c->c2;
-    R.gm = c->gm;
-    R.n_free = (int)c->n_free;
-    R.v_off = b->v_off[p];
-    R.free_off = b->free_off[p];
-    R.rinv_off = r_off[p];
-    R.g_off = g_off[p];
   }
   int dev = 0, ncu = 256;
   if (hipGetDevice(&dev) == hipSuccess) hipDeviceGetAttribute(&ncu, hipDeviceAttributeMultiprocessorCount, dev);
@@ -1961,8 +1973,8 @@ void dpo_batch_destroy(dpo_batch* b) {
   if (!b) return;
   if (b->stream) hipStreamSynchronize(b->stream);
   for (dpo_ctx* c : b->ctx) dpo_destroy(c);
-  void* bufs[] = {b->Va, b->Vb, b->ang, b->thr, b->free_all, b->rinv_all, b->g_all,
-                  b->d_probs, b->d_tile_begin, b->d_tile_run, b->d_run, b->d_done, b->d_partial, b->d_resid};
+  void* bufs[] = {b->Va, b->Vb, b->ang, b->thr, b->d_sweeps,
+                  b->d_tile_begin, b->d_tile_run, b->d_run, b->d_done, b->d_partial, b->d_resid};
   for (void* v : bufs)
     if (v) hipFree(v);
   if (b->stream) hipStreamDestroy(b->stream);
@@ -2056,10 +2068,10 @@ int dpo_batch_time_config(dpo_batch* b, int32_t block, int32_t sweeps_per_graph,
   std::vector<int> run(n);
   for (int p = 0; p < n; p++) run[p] = p;
   int n_tiles = 0;
-  if ((rc = batch_tables(b, block, run, &n_tiles)) != DPO_OK) return rc;
+  if ((rc = batch_tables(b, block, run, false, &n_tiles)) != DPO_OK) return rc;
   BHIP_TRY(b, hipMemsetAsync(b->d_done, 0, sizeof(int) * n, b->stream));
   hipGraphExec_t exec = nullptr;
-  if ((rc = batch_graph(b, batch_args(b, -1.0, n, n_tiles, false), block, sweeps_per_graph, &exec)) != DPO_OK) return rc;
+  if ((rc = batch_graph(b, batch_args(b, -1.0, run, n_tiles), block, sweeps_per_graph, &exec)) != DPO_OK) return rc;
   // replays as the solver issues them: graph, read-back of the stop flags, sync
   std::vector<int> flags(n, 0);
   hipError_t e = hipGraphLaunch(exec, b->stream);  // warm-up

@@ -9,56 +9,44 @@
 namespace dpo {
 
 // One workgroup per tile of the running problems (numbered problem by
-// problem, XCD-contiguous); the problem's record holds offsets into the
-// concatenated buffers, whose bases are kernel arguments.  The tile's problem
-// is one table lookup, so a workgroup's set-up waits on two dependent loads
-// (table entry, then record) whatever the number of running problems.
+// problem, XCD-contiguous), sweeping it with the problem's own arguments.
+// The tile's problem is one table lookup, so a workgroup's set-up waits on
+// two dependent loads (table entry, then arguments) whatever the number of
+// running problems.
 template <int kMode>
 __global__ __launch_bounds__(kMaxBlock) __attribute__((amdgpu_waves_per_eu(8))) void k_batch_sweep(BatchArgs B, int parity, int want_resid) {
   extern __shared__ float4 dyn_lds[];
   const int tile = xcd_tile(blockIdx.x, gridDim.x);
-  const BatchProblem& R = B.probs[B.tile_run[tile]];
-  SweepArgs a;
-  a.G = R.G;
-  a.P = R.P;
-  a.V_in = (parity ? B.Vb : B.Va) + R.v_off;
-  a.V_out = (parity ? B.Va : B.Vb) + R.v_off;
-  a.pol_ang = B.ang_all ? B.ang_all + R.v_off : nullptr;
-  a.pol_thr = B.thr_all ? B.thr_all + R.v_off : nullptr;
-  a.free_node = B.free_all + R.free_off;
-  a.n_free = R.n_free;
-  a.rinv = B.rinv_all + R.rinv_off;
-  a.g1tab = B.g_all + R.g_off;
-  a.g2tab = B.g_all + R.g_off + R.G.n[3];
-  a.c0 = R.c0;
-  a.c1 = R.c1;
-  a.c2 = R.c2;
-  a.gm = R.gm;
-  a.tab_sin = B.tab;
-  a.tab_cos = B.tab + B.n_ang;
-  a.tab_ang = B.tab + 2 * B.n_ang;
-  a.n_ang = B.n_ang;
-  a.n_golden = B.n_golden;
-  a.half_width = B.half_width;
-  a.rot_scan = B.rot_scan;
+  const int k = __builtin_amdgcn_readfirstlane(B.tile_run[tile]);
+  const ConstArgs p = (ConstArgs)(B.sweeps + parity * B.n_run + k);
+  SweepArgs a = *(const SweepArgs*)p;
+  a.V_in = in_global(a.V_in);
+  a.V_out = in_global(a.V_out);
+  a.pol_ang = in_global(a.pol_ang);
+  a.pol_thr = in_global(a.pol_thr);
+  a.sweep_node = in_global(a.sweep_node);
+  a.one_cell = in_global(a.one_cell);
+  a.rinv = in_global(a.rinv);
+  a.drift0 = in_global(a.drift0);
+  a.drift1 = in_global(a.drift1);
+  a.drift2 = in_global(a.drift2);
+  a.mrow = in_global(a.mrow);
+  a.tab_sin = in_global(a.tab_sin);
+  a.tab_cos = in_global(a.tab_cos);
+  a.tab_ang = in_global(a.tab_ang);
+  a.rot_scan = in_global(a.rot_scan);
+  // what a batched sweep does not have
+  a.drift3 = nullptr;
+  a.seed = a.walk_from = a.pol_ang_in = nullptr;
+  a.pol_thr_in = nullptr;
+  a.fb_list = nullptr;
   a.desc_code = nullptr;
   a.desc16 = nullptr;
   a.desc_pk = nullptr;
-  a.desc_pk_in = nullptr;
-  a.desc_dense = 0;
-  a.seed = nullptr;
-  a.pol_ang_in = nullptr;
-  a.pol_thr_in = nullptr;
-  a.fb_list = nullptr;
-  a.fb_count = nullptr;
-  a.walk_from = nullptr;
-  a.eval_acc = nullptr;
-  const int t = (tile - R.tile_begin) * blockDim.x + threadIdx.x;
-  double rel = 0, sum = 0, mabs = 0, bad = 0;
-  int fell_back = 0, deferred = 0, evals = 0;
-  if (t < a.n_free) fast_node<kMode>(a, t, dyn_lds, rel, sum, mabs, bad, fell_back, deferred, evals);
+  NodeSums S;
+  sweep_nodes<kMode>(a, tile - B.tile_begin[k], dyn_lds, want_resid != 0, S);
   // only the last sweep of a graph replay feeds the stop decision
-  if (want_resid) block_residual(rel, sum, mabs, bad, (double)fell_back, B.partial, tile);
+  if (want_resid) block_residual(S.rel, S.sum, S.mabs, S.bad, (double)S.fell_back, B.partial, tile);
 }
 
 // One workgroup per running problem: FP64 reduction of its tiles' partials
@@ -96,7 +84,7 @@ __global__ __launch_bounds__(kBlock) void k_batch_reduce(BatchArgs B) {
 }
 
 hipError_t launch_batch_sweep(const BatchArgs& b, int mode, int block, int parity, int want_resid, hipStream_t s) {
-  const size_t lds = sizeof(float4) * 4 * block;
+  const size_t lds = sweep_lds_bytes(block, b.n_ang);
   if (mode == 0) hipLaunchKernelGGL(k_batch_sweep<0>, dim3(b.n_tiles), dim3(block), lds, s, b, parity, want_resid);
   else hipLaunchKernelGGL(k_batch_sweep<1>, dim3(b.n_tiles), dim3(block), lds, s, b, parity, want_resid);
   return hipGetLastError();

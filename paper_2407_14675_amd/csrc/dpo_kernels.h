@@ -26,10 +26,23 @@ struct SweepArgs {
   int* fb_count;              // their count (zeroed before the sweep)
   const uint32_t* free_node;  // packed coordinates (8 bits per axis, r lowest) of the free nodes
   int n_free;
-  // per-axis / per-plane tables (FP64 1/r; thrust displacement per unit sin/cos per mass plane)
+  // factorised sweeps: the free list reordered within chunks of kOrderChunk
+  // entries, of which the first one_cell[k] of chunk k are nodes whose thrust
+  // feet share one cell; sweep_pos: an entry's place in node order in its chunk
+  const uint32_t* sweep_node;
+  const uint16_t* sweep_pos;
+  const int* one_cell;
+  // tables of the node terms (see node_terms_at): FP64 1/r per r node; drift along r
+  // per v_r node, along v_r per (v_t, r), along v_t times r per (v_t, v_r) in
+  // FP64, along theta (crown, else null) per (v_t, r); per mass plane the thrust
+  // displacement per unit sin and cos, the m cell coordinate of the thrust feet and
+  // the byte offset of their lower plane (bit 0: inside; bit 1: it is the node's own)
   const double* rinv;
-  const float* g1tab;
-  const float* g2tab;
+  const float* drift0;
+  const float* drift1;
+  const double* drift2;
+  const float* drift3;
+  const float4* mrow;
   double c0, c1, c2, c3;  // dt / h_k for axes r, v_r, v_t and axis 3
   const float* qnode;     // crown problem: dt times the orbital-element running cost per node, nullable
   float gm;           // thrust displacement along m (cells)
@@ -39,6 +52,7 @@ struct SweepArgs {
   int n_ang;
   int n_golden;
   float half_width;  // golden bracket half width, 2*pi/n_scan
+  float scan_y0, scan_k;  // 1 - cos(pi/n_ang) and n_ang/(2 pi) (see scan_window)
   const float* rot_scan;   // golden-section rotation constants for half_width (see golden())
   const float* rot_local;  // the same for local_half_width
   int n_local;
@@ -73,6 +87,8 @@ struct SweepArgs {
   double w_time, w_fuel, lambda;
 };
 
+constexpr int kOrderChunk = 4096;  // entries of the free list ordered together (a multiple of 64)
+
 inline int blocks_for(long long n, int per = kBlock) { return (int)((n + per - 1) / per); }
 
 constexpr uint16_t kDescOut = 1u << 12;
@@ -100,41 +116,14 @@ constexpr int kWaveStates = 8192;
 constexpr int kResidStage = 256;          // workgroups of the first stage of the residual reduction
 constexpr int kDescReach = 31;           // largest cell offset the compact code holds
 
-// Per-problem record of the batched sweep (device table).  It holds no
-// pointers: every array of the batch is one concatenated allocation passed
-// as a kernel argument, and the record gives this problem's offsets into it.
-struct BatchProblem {
-  Grid G;
-  Phys P;
-  double c0, c1, c2;
-  float gm;
-  int n_free;
-  long long v_off;  // offset of node 0 in the value / policy arrays
-  int free_off;     // offset in the concatenated free-node list
-  int rinv_off;     // offset in the concatenated 1/r table
-  int g_off;        // offset in the concatenated thrust tables ([2][n_m] per problem)
-  int tile_begin;   // first tile of this problem
-};
-
 struct BatchArgs {
-  const BatchProblem* probs;  // records of the running problems, in run order (n_run entries)
+  const SweepArgs* sweeps;  // sweep arguments of the running problems, in run order, buffer A to B, then B to A
   const int* run;             // problem number of each running problem (n_run entries)
   const int* tile_begin;      // first tile of each running problem (n_run + 1 entries)
   const int* tile_run;        // running problem of each tile (n_tiles entries)
   int n_run;
   int n_tiles;
-  const uint32_t* free_all;
-  const double* rinv_all;
-  const float* g_all;
-  float* Va;  // value buffer A (concatenated)
-  float* Vb;  // value buffer B
-  float* ang_all;
-  uint8_t* thr_all;
-  const float* tab;  // shared search table [3][n_ang]
-  int n_ang;
-  int n_golden;
-  float half_width;
-  const float* rot_scan;
+  int n_ang;      // shared search table
   int* done;      // per problem: 0 running, 1 converged, 2 non-finite values
   double* partial;
   double* resid;  // kPartial per problem
@@ -150,6 +139,12 @@ hipError_t launch_classify(const Grid& G, const TargetBox& tb, const uint8_t* ma
 int compact_chunks(int N);
 hipError_t launch_compact(const Grid& G, const uint8_t* kind, int N, int* counts, int* offsets,
                           uint32_t* free_node, hipStream_t s);
+// Fills the node-term tables a points to (its own fields, written) from the
+// formulas; g1tab, g2tab: thrust displacement per mass plane.
+hipError_t launch_node_tables(const SweepArgs& a, const float* g1tab, const float* g2tab, hipStream_t s);
+// Fills sweep_node, sweep_pos and one_cell (see SweepArgs) from the free list.
+hipError_t launch_order_free(const SweepArgs& a, uint32_t* sweep_node, uint16_t* sweep_pos, int* one_cell,
+                             hipStream_t s);
 hipError_t launch_init_value(const uint8_t* kind, float M, float* V, int N, hipStream_t s);
 // Direct-path sweep; mode 0 table, 1 scan + golden, 2 seeded, 3 table walk
 // (the integrator comes from a.P.heun).

@@ -122,6 +122,101 @@ __global__ __launch_bounds__(kBlock) void k_scatter_free(Grid G, const uint8_t* 
   }
 }
 
+// The node-term tables, by the formulas; one entry of each per thread.
+__global__ __launch_bounds__(kBlock) void k_node_tables(SweepArgs a, const float* __restrict__ g1tab,
+                                                        const float* __restrict__ g2tab) {
+#pragma clang fp contract(off)
+  const Grid& G = a.G;
+  const int e = blockIdx.x * kBlock + threadIdx.x;
+  NodeTerms T;
+  T.i[1] = T.i[3] = 0;
+  if (e < G.n[0] * G.n[2]) {
+    T.i[0] = e % G.n[0];
+    T.i[2] = e / G.n[0];
+    node_terms_calc(a, g1tab, g2tab, T);
+    const_cast<float*>(a.drift1)[e] = T.drift[1];
+    if (a.drift3) const_cast<float*>(a.drift3)[e] = T.drift[3];
+  }
+  if (e < G.n[1] * G.n[2]) {
+    const double vr = G.lo[1] + (double)(e % G.n[1]) * G.h[1];
+    const double vt = G.lo[2] + (double)(e / G.n[1]) * G.h[2];
+    const_cast<double*>(a.drift2)[e] = a.P.model != 1 ? -a.c2 * vr * vt : 0.0;
+  }
+  if (e < G.n[1]) const_cast<float*>(a.drift0)[e] = drift_r(a, e);
+  if (e < G.n[3]) {
+    int bm = 0;
+    float tm = 0.0f;
+    const bool ok = axis_cell(e, G.n[3], a.gm, bm, tm);
+    const int lo = ok ? bm : e;
+    const uint32_t w = 4u * (uint32_t)lo * (uint32_t)G.st[3] + (ok ? 1u : 0u) + (lo == e ? 2u : 0u);
+    const_cast<float4*>(a.mrow)[e] = make_float4(g1tab[e], g2tab[e], tm, __uint_as_float(w));
+  }
+}
+
+// Order of the free list for the factorised sweeps.  Whether a node's thrust
+// feet share one cell depends on the grid and the physics alone, and the 64
+// consecutive nodes of a wave nearly always hold one whose feet do not (95 %
+// of the waves at 5-15 % of the nodes), so that every wave would run the
+// general form of the search.  Within chunks of kOrderChunk entries (the
+// value rows of a chunk stay in one XCD's L2) the one-cell nodes come first.
+__global__ __launch_bounds__(kBlock) void k_order_free(SweepArgs a, uint32_t* __restrict__ sweep_node,
+                                                       uint16_t* __restrict__ sweep_pos, int* __restrict__ one_cell) {
+  __shared__ int wave_one[kBlock / 64], wave_rest[kBlock / 64];
+  const int base = blockIdx.x * kOrderChunk, n = min(kOrderChunk, a.n_free - base);
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  // one contiguous slice of the chunk per wave
+  const int slice = kOrderChunk / (kBlock / 64), lo = wave * slice, hi = min(lo + slice, n);
+  int ones = 0, rest = 0;
+  unsigned long long kinds[kOrderChunk / kBlock];
+#pragma unroll
+  for (int r = 0; r < slice / 64; r++) {
+    const int e = lo + r * 64 + lane;
+    bool one = false;
+    if (e < hi) {
+      NodeTerms T;
+      node_terms_tab(a, a.free_node[base + e], T);
+      FeetCells C;
+      feet_cells<false>(a, T, C);
+      one = C.one_cell();
+    }
+    kinds[r] = __ballot(one);
+    ones += __popcll(kinds[r]);
+    rest += __popcll(__ballot(e < hi && !one));
+  }
+  if (lane == 0) {
+    wave_one[wave] = ones;
+    wave_rest[wave] = rest;
+  }
+  __syncthreads();
+  if (threadIdx.x == 0) {
+    int total = 0;
+    for (int w = 0; w < kBlock / 64; w++) total += wave_one[w];
+    one_cell[blockIdx.x] = total;
+  }
+  int at_one = 0, at_rest = 0;
+  for (int w = 0; w < kBlock / 64; w++) {
+    at_rest += wave_one[w];
+    if (w < wave) {
+      at_one += wave_one[w];
+      at_rest += wave_rest[w];
+    }
+  }
+#pragma unroll
+  for (int r = 0; r < slice / 64; r++) {
+    const int e = lo + r * 64 + lane;
+    const unsigned long long below = (1ull << lane) - 1ull;
+    const bool one = (kinds[r] >> lane) & 1ull;
+    const unsigned long long others = __ballot(e < hi && !one);
+    if (e < hi) {
+      const int to = base + (one ? at_one + __popcll(kinds[r] & below) : at_rest + __popcll(others & below));
+      sweep_node[to] = a.free_node[base + e];
+      sweep_pos[to] = (uint16_t)e;
+    }
+    at_one += __popcll(kinds[r]);
+    at_rest += __popcll(others);
+  }
+}
+
 __global__ __launch_bounds__(kBlock) void k_init_value(const uint8_t* __restrict__ kind, float M,
                                                        float* __restrict__ V, int N) {
   const int j = blockIdx.x * kBlock + threadIdx.x;
@@ -178,30 +273,18 @@ __global__ __launch_bounds__(kBlock) void k_sweep_direct(SweepArgs a) {
 }
 
 // Factorised-path sweep; the workgroup size is chosen at launch (64..512)
-// and the region pairs live in dynamic LDS (4 * blockDim.x float4).
+// and the region pairs live in dynamic LDS.
 template <int kMode>
 __global__ __launch_bounds__(kMaxBlock) __attribute__((amdgpu_waves_per_eu(8))) void k_sweep_fast(SweepArgs a) {
   extern __shared__ float4 dyn_lds[];
   const int tile = xcd_tile(blockIdx.x, gridDim.x);
-  const int t = tile * blockDim.x + threadIdx.x;
-  double rel = 0, sum = 0, mabs = 0, bad = 0;
-  int fell_back = 0, deferred = 0, evals = 0;
-  if (t < a.n_free) fast_node<kMode>(a, t, dyn_lds, rel, sum, mabs, bad, fell_back, deferred, evals);
-  if (kMode == 3 && a.eval_acc) block_add_count(evals, a.eval_acc);
-  if (kMode == 2 && a.fb_list) {
-    // append the wave's deferred nodes with one atomic per wave
-    const unsigned long long bal = __ballot(deferred);
-    if (bal) {
-      const int lane = threadIdx.x & 63;
-      int base = 0;
-      if (lane == 0) base = atomicAdd(a.fb_count, __popcll(bal));
-      base = __shfl(base, 0, 64);
-      if (deferred) a.fb_list[base + __popcll(bal & ((1ull << lane) - 1ull))] = t;
-    }
-  }
+  NodeSums S;
+  sweep_nodes<kMode>(a, tile, dyn_lds, a.partial != nullptr, S);
+  if (kMode == 3 && a.eval_acc) block_add_count(S.evals, a.eval_acc);
   // a null partial buffer (value-iteration sweeps between checks) skips the residual;
   // the fifth entry: seeded fallbacks, or the walk's thrust evaluations
-  if (a.partial) block_residual(rel, sum, mabs, bad, (double)(kMode == 3 ? evals : fell_back), a.partial, blockIdx.x);
+  if (a.partial)
+    block_residual(S.rel, S.sum, S.mabs, S.bad, (double)(kMode == 3 ? S.evals : S.fell_back), a.partial, blockIdx.x);
 }
 
 // Second pass of the seeded sweep: the full search at the nodes the first
@@ -211,11 +294,10 @@ __global__ __launch_bounds__(kMaxBlock) __attribute__((amdgpu_waves_per_eu(8))) 
 __global__ __launch_bounds__(kMaxBlock) __attribute__((amdgpu_waves_per_eu(8))) void k_sweep_fallback(SweepArgs a) {
   extern __shared__ float4 dyn_lds[];
   const int count = *a.fb_count;
-  double rel = 0, sum = 0, mabs = 0, bad = 0;
-  int unused = 0, unused2 = 0, unused3 = 0;
+  NodeSums S;
   for (int k = blockIdx.x * blockDim.x + threadIdx.x; k < count; k += gridDim.x * blockDim.x)
-    fast_node<1>(a, a.fb_list[k], dyn_lds, rel, sum, mabs, bad, unused, unused2, unused3);
-  block_residual(rel, sum, mabs, bad, 0.0, a.partial, blockIdx.x);
+    fast_node<1, false>(a, a.fb_list[k], a.sweep_node[a.fb_list[k]], dyn_lds, nullptr, true, S);
+  block_residual(S.rel, S.sum, S.mabs, S.bad, 0.0, a.partial, blockIdx.x);
 }
 
 __global__ void k_zero_count(int* count) { *count = 0; }
@@ -766,6 +848,17 @@ hipError_t launch_compact(const Grid& G, const uint8_t* kind, int N, int* counts
   return hipGetLastError();
 }
 
+hipError_t launch_node_tables(const SweepArgs& a, const float* g1tab, const float* g2tab, hipStream_t s) {
+  const int* n = a.G.n;
+  const int most = std::max(std::max(n[0], n[1]) * n[2], n[3]);
+  DPO_LAUNCH(k_node_tables, blocks_for(most), kBlock, s, a, g1tab, g2tab);
+}
+
+hipError_t launch_order_free(const SweepArgs& a, uint32_t* sweep_node, uint16_t* sweep_pos, int* one_cell,
+                             hipStream_t s) {
+  DPO_LAUNCH(k_order_free, blocks_for(a.n_free, kOrderChunk), kBlock, s, a, sweep_node, sweep_pos, one_cell);
+}
+
 hipError_t launch_init_value(const uint8_t* kind, float M, float* V, int N, hipStream_t s) {
   DPO_LAUNCH(k_init_value, blocks_for(N), kBlock, s, kind, M, V, N);
 }
@@ -794,7 +887,7 @@ hipError_t launch_sum_counts(const unsigned long long* acc, int n, unsigned long
 
 hipError_t launch_sweep_fast(const SweepArgs& a, int mode, int block, hipStream_t s) {
   const int nb = blocks_for(a.n_free, block);
-  const size_t lds = sizeof(float4) * 4 * block;
+  const size_t lds = sweep_lds_bytes(block, a.n_ang);
   if (mode == 0) hipLaunchKernelGGL(k_sweep_fast<0>, dim3(nb), dim3(block), lds, s, a);
   else if (mode == 1) hipLaunchKernelGGL(k_sweep_fast<1>, dim3(nb), dim3(block), lds, s, a);
   else if (mode == 2) hipLaunchKernelGGL(k_sweep_fast<2>, dim3(nb), dim3(block), lds, s, a);
@@ -805,7 +898,7 @@ hipError_t launch_sweep_fast(const SweepArgs& a, int mode, int block, hipStream_
 hipError_t launch_zero_count(int* count, hipStream_t s) { DPO_LAUNCH(k_zero_count, 1, 1, s, count); }
 
 hipError_t launch_sweep_fallback(const SweepArgs& a, int block, int blocks, hipStream_t s) {
-  const size_t lds = 4 * (size_t)block * sizeof(float4);
+  const size_t lds = sweep_lds_bytes(block, a.n_ang);
   hipLaunchKernelGGL(k_sweep_fallback, dim3(blocks), dim3(block), lds, s, a);
   return hipGetLastError();
 }

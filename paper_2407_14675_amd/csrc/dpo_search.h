@@ -7,6 +7,8 @@
 // and golden-section refinement).
 #pragma once
 
+#include <type_traits>
+
 #include "dpo_kernels.h"
 
 namespace dpo {
@@ -26,8 +28,9 @@ __device__ inline float drift_r(const SweepArgs& a, int i1) {
   return (float)(a.c0 * vr);
 }
 
-// Node terms of the node whose grid coordinates are already in T.i.
-__device__ inline void node_terms_at(const SweepArgs& a, NodeTerms& T) {
+// Node terms of the node whose grid coordinates are already in T.i, by the
+// formulas (what the context's tables are filled with).
+__device__ inline void node_terms_calc(const SweepArgs& a, const float* g1tab, const float* g2tab, NodeTerms& T) {
 #pragma clang fp contract(off)
   T.drift[3] = 0.0f;
   if (a.P.model != 1) {
@@ -42,8 +45,23 @@ __device__ inline void node_terms_at(const SweepArgs& a, NodeTerms& T) {
   } else {
     T.drift[0] = T.drift[1] = T.drift[2] = 0.0f;
   }
-  T.g1 = a.g1tab[T.i[3]];
-  T.g2 = a.g2tab[T.i[3]];
+  T.g1 = g1tab[T.i[3]];
+  T.g2 = g2tab[T.i[3]];
+  T.gm = a.gm;
+}
+
+// The same from the context's tables: every term depends on one or two of the
+// coordinates only (the drift along v_t is one FP64 product of two of them),
+// so a node reads a few cached entries instead of some twenty FP64 operations.
+__device__ inline void node_terms_at(const SweepArgs& a, NodeTerms& T) {
+#pragma clang fp contract(off)
+  T.drift[0] = a.drift0[T.i[1]];
+  T.drift[1] = a.drift1[__umul24(T.i[2], a.G.n[0]) + T.i[0]];
+  T.drift[2] = (float)(a.drift2[__umul24(T.i[2], a.G.n[1]) + T.i[1]] * a.rinv[T.i[0]]);
+  T.drift[3] = a.drift3 ? a.drift3[__umul24(T.i[2], a.G.n[0]) + T.i[0]] : 0.0f;
+  const float4 m = a.mrow[T.i[3]];
+  T.g1 = m.x;
+  T.g2 = m.y;
   T.gm = a.gm;
 }
 
@@ -52,6 +70,13 @@ __device__ inline int node_terms_tab(const SweepArgs& a, uint32_t packed, NodeTe
   node_terms_at(a, T);
   return j;
 }
+
+// A table that no kernel of the launch writes, read at an index all lanes
+// share: through the constant address space, so that the loads are scalar
+// also where the kernel has stored to memory before (the compiler must
+// otherwise take any store as one that may change the table).
+typedef const __attribute__((address_space(4))) float* ConstTable;
+__device__ inline ConstTable const_table(const float* p) { return (ConstTable)p; }
 
 // Golden-section refinement around the centre angle u0 (sin/cos s0, c0) on
 // [u0 - half, u0 + half]: two interior points u0 -+ half*rho^3, then one new
@@ -69,8 +94,9 @@ struct GoldenState {
 };
 
 template <class QF>
-__device__ inline void golden(const QF& qf, float s0, float c0, float half, int steps, const float* __restrict__ rot,
+__device__ inline void golden(const QF& qf, float s0, float c0, float half, int steps, const float* rot_table,
                               GoldenState& g) {
+  const ConstTable rot = const_table(rot_table);
   const float rho = 0.6180339887498949f;
   const float sp = rot[0], cp = rot[1];
   // the two interior points u0 -+ half*rho^3 (rho^3 = 2 rho - 1)
@@ -93,20 +119,22 @@ __device__ inline void golden(const QF& qf, float s0, float c0, float half, int 
   }
   // K: the interior point kept from the previous step; N: the point just
   // evaluated, on the left of K when nl.  Each step keeps the lower interior
-  // point and places the new one symmetrically, at distance 2*half*rho^(k+4)
-  // from it, by rotating (sin, cos) of the kept point.
+  // point (the right one unless the left is strictly lower) and places the
+  // new one symmetrically, at distance 2*half*rho^(k+4) from it, by rotating
+  // (sin, cos) of the kept point.  The decision is two compares and lane-mask
+  // logic on the scalar unit; no value is selected for it.
   bool nl = true;
   float delta = 2.0f * half * 0.1458980337503155f;  // 2*half*rho^4
   for (int it = 0; it < steps; it++) {
     const float sd = rot[2 + 2 * it], cd = rot[3 + 2 * it];
-    const float f_left = nl ? fN : fK, f_right = nl ? fK : fN;
-    const bool left = f_left < f_right;  // the left point is the lower one
-    const bool keepN = left == nl;
+    const bool n_lower = fN < fK, k_lower = fK < fN;
+    const bool keepN = (nl & n_lower) | (!nl & !k_lower);
+    const bool left = keepN == nl;  // the left point is the lower one
     const float xk = keepN ? xN : xK, sk = keepN ? sN : sK, ck = keepN ? cN : cK, fk = keepN ? fN : fK;
     const float sdd = left ? -sd : sd;
     sN = fmaf(sk, cd, ck * sdd);
     cN = fmaf(ck, cd, -sk * sdd);
-    xN = left ? xk - delta : xk + delta;
+    xN = xk + (left ? -delta : delta);
     delta *= rho;
     xK = xk;
     sK = sk;
@@ -135,9 +163,10 @@ __device__ inline void scan_table(const QF& qf, const SweepArgs& a, float& bq, i
   bq = INFINITY;
   bk = 0;
   if (!kWave) {
+    const ConstTable ts = const_table(a.tab_sin), tc = const_table(a.tab_cos);
 #pragma unroll 8
     for (int k = 0; k < a.n_ang; k++) {
-      const float q = qf(a.tab_sin[k], a.tab_cos[k]);
+      const float q = qf(ts[k], tc[k]);
       if (q < bq) {
         bq = q;
         bk = k;
@@ -172,13 +201,10 @@ struct Choice {
   int thr;       // 1 = thrust
 };
 
-// Full search: scan, golden section around the best sample (if n_golden > 0),
-// then thrust iff strictly below the coast value qc.
-template <bool kWave = false, class QF>
-__device__ inline void full_search(const QF& qf, const SweepArgs& a, float qc, Choice& ch) {
-  float bq;
-  int bk;
-  scan_table<kWave>(qf, a, bq, bk);
+// Full search: scan, golden section around the best sample bk of value bq (if
+// n_golden > 0), then thrust iff strictly below the coast value qc.
+template <class QF>
+__device__ inline void refine_search(const QF& qf, const SweepArgs& a, float bq, int bk, float qc, Choice& ch) {
   GoldenState g{bq, 0.0f, a.tab_sin[bk], a.tab_cos[bk]};
   if (a.n_golden > 0) golden(qf, a.tab_sin[bk], a.tab_cos[bk], a.half_width, a.n_golden, a.rot_scan, g);
   ch.thr = g.best_q < qc ? 1 : 0;
@@ -188,17 +214,29 @@ __device__ inline void full_search(const QF& qf, const SweepArgs& a, float qc, C
   ch.cs = g.best_c;
 }
 
-// Tabulated search: first strict minimum over the table, coast on ties.
 template <bool kWave = false, class QF>
-__device__ inline void table_search(const QF& qf, const SweepArgs& a, float qc, Choice& ch) {
+__device__ inline void full_search(const QF& qf, const SweepArgs& a, float qc, Choice& ch) {
   float bq;
   int bk;
   scan_table<kWave>(qf, a, bq, bk);
+  refine_search(qf, a, bq, bk, qc, ch);
+}
+
+// Tabulated search: first strict minimum over the table, coast on ties.
+__device__ inline void table_choice(const SweepArgs& a, float bq, int bk, float qc, Choice& ch) {
   ch.thr = bq < qc ? 1 : 0;
   ch.v = ch.thr ? bq : qc;
   ch.ang = a.tab_ang[bk];
   ch.sn = a.tab_sin[bk];
   ch.cs = a.tab_cos[bk];
+}
+
+template <bool kWave = false, class QF>
+__device__ inline void table_search(const QF& qf, const SweepArgs& a, float qc, Choice& ch) {
+  float bq;
+  int bk;
+  scan_table<kWave>(qf, a, bq, bk);
+  table_choice(a, bq, bk, qc, ch);
 }
 
 // Seeded local search: the seed angle, then a golden section with n_local - 3
@@ -454,10 +492,57 @@ __device__ inline float lerp_pair(const float* p, float t) {
   return lerp(v.lo, v.hi, t);
 }
 
+// The cells a node's thrust feet fall in.
+struct FeetCells {
+  bool ok_r, ok_m;    // inside along r; under thrust, along m
+  bool coast_lo;      // the coast foot's plane i_m is the lower plane of the thrust feet
+  int br;             // r cell, shared by every control
+  uint32_t plane;     // byte offset of the thrust feet's lower mass plane (i_m outside)
+  float tr, tm;       // cell coordinates along r and (thrust) m
+  Regions Rv, Rt;
+  // every thrust foot (and the coast foot, which lies between them) in one cell, or outside
+  __device__ bool one_cell() const { return Rv.bnd == INFINITY && Rt.bnd == INFINITY; }
+};
+
+// axis_regions of a node known to have one region.
+__device__ inline Regions axis_one_region(int i, int n, float d, float g) {
+  const float ag = fabsf(g) + 1e-6f;
+  const float lo = d - ag, hi = d + ag;
+  Regions R;
+  R.ok0 = !(hi < (float)(-i) || lo > (float)(n - 1 - i));
+  R.ok1 = false;
+  R.b0 = R.ok0 ? i + (int)floorf(hi) : 0;
+  R.bnd = INFINITY;
+  return R;
+}
+
+template <bool kOne>
+__device__ inline void feet_cells(const SweepArgs& a, const NodeTerms& T, FeetCells& C) {
+  const Grid& G = a.G;
+  C.br = 0;
+  C.tr = 0.0f;
+  C.ok_r = axis_cell(T.i[0], G.n[0], T.drift[0], C.br, C.tr);
+  // m cell under thrust; the coast foot stays on plane i_m
+  const float4 m = a.mrow[T.i[3]];
+  const uint32_t w = __float_as_uint(m.w);
+  C.tm = m.z;
+  C.plane = w & ~3u;
+  C.ok_m = w & 1u;
+  C.coast_lo = w & 2u;
+  C.Rv = kOne ? axis_one_region(T.i[1], G.n[1], T.drift[1], T.g1) : axis_regions(T.i[1], G.n[1], T.drift[1], T.g1);
+  C.Rt = kOne ? axis_one_region(T.i[2], G.n[2], T.drift[2], T.g2) : axis_regions(T.i[2], G.n[2], T.drift[2], T.g2);
+}
+
+// A corner pair at a byte offset from V (below 2^32: at most 2^30 nodes), so
+// that the load takes a scalar base and one 32-bit offset.
+__device__ inline CornerPair pair_at(const float* __restrict__ V, uint32_t byte_off) {
+  return *reinterpret_cast<const CornerPair*>(reinterpret_cast<const char*>(V) + byte_off);
+}
+
 // Per-node set-up of the thrust evaluations; returns the coast Q, which is
 // the same Q1 value read from the patch (plane i_m, coast cell).
 // lds: 4 * blockDim.x float4, laid out [region pair][thread].
-__device__ inline float fast_setup(const SweepArgs& a, const NodeTerms& T, float4* lds, FastNode& F) {
+__device__ inline float fast_setup(const SweepArgs& a, const NodeTerms& T, const FeetCells& C, float4* lds, FastNode& F) {
   const Grid& G = a.G;
   F.g1 = T.g1;
   F.g2 = T.g2;
@@ -466,42 +551,33 @@ __device__ inline float fast_setup(const SweepArgs& a, const NodeTerms& T, float
   F.offv = 2 * (int)blockDim.x * (int)sizeof(float4);
   F.offt = (int)blockDim.x * (int)sizeof(float4);
   F.coef = reinterpret_cast<const char*>(lds + threadIdx.x);
-  // r cell, shared by every control
-  int br = 0, bm = 0;
-  float tr = 0.0f, tm = 0.0f;
-  const bool ok_r = axis_cell(T.i[0], G.n[0], T.drift[0], br, tr);
-  // m cell under thrust; the coast foot stays on plane i_m
-  const bool ok_m = axis_cell(T.i[3], G.n[3], T.gm, bm, tm);
-  const int m_lo = ok_m ? bm : T.i[3];
-  const int m_hi = ok_m ? bm + 1 : T.i[3];
-  const int coast_plane = T.i[3];  // either m_lo or m_hi
-  const Regions Rv = axis_regions(T.i[1], G.n[1], T.drift[1], T.g1);
-  const Regions Rt = axis_regions(T.i[2], G.n[2], T.drift[2], T.g2);
+  const bool ok_r = C.ok_r, ok_m = C.ok_m;
+  const float tr = C.tr, tm = C.tm;
+  const Regions& Rv = C.Rv;
+  const Regions& Rt = C.Rt;
   F.bv = Rv.bnd;
   F.bt = Rt.bnd;
   const float qM = fmaf(a.P.gamma, a.P.M, a.P.q_thr);
   float W[3][3], Wc[3][3];
   if (ok_r) {
-    const float* __restrict__ base = a.V_in + br + m_lo * G.st[3];
-    const int so = (m_hi - m_lo) * G.st[3];
+    const uint32_t base = C.plane + 4u * (uint32_t)C.br, so = ok_m ? 4u * (uint32_t)G.st[3] : 0u;
 #pragma unroll
     for (int p = 0; p < 3; p++) {
-      const int v = min(max(Rv.b0 + p, 0), G.n[1] - 1);
+      const uint32_t v = base + __umul24(min(max(Rv.b0 + p, 0), G.n[1] - 1), 4 * G.st[1]);
       // the row's six corner pairs are loaded before any of them is used,
       // so that their latencies overlap
       CornerPair lo[3], hi[3];
 #pragma unroll
       for (int q = 0; q < 3; q++) {
-        const int w = min(max(Rt.b0 + q, 0), G.n[2] - 1);
-        const float* pp = base + v * G.st[1] + w * G.st[2];
-        lo[q] = *reinterpret_cast<const CornerPair*>(pp);
-        hi[q] = *reinterpret_cast<const CornerPair*>(pp + so);
+        const uint32_t o = v + __umul24(min(max(Rt.b0 + q, 0), G.n[2] - 1), 4 * G.st[2]);
+        lo[q] = pair_at(a.V_in, o);
+        hi[q] = pair_at(a.V_in, o + so);
       }
 #pragma unroll
       for (int q = 0; q < 3; q++) {
         const float l = lerp(lo[q].lo, lo[q].hi, tr), h = lerp(hi[q].lo, hi[q].hi, tr);
         W[p][q] = lerp(l, h, tm);
-        Wc[p][q] = coast_plane == m_lo ? l : h;
+        Wc[p][q] = C.coast_lo ? l : h;
       }
     }
   }
@@ -547,42 +623,307 @@ __device__ inline float fast_setup(const SweepArgs& a, const NodeTerms& T, float
 }
 
 
-// One free node of a sweep on the factorised path: search, outputs and the
-// residual contributions.  kMode: 0 tabulated, 1 scan + golden, 2 seeded.
-template <int kMode>
-__device__ inline void fast_node(const SweepArgs& a, int t, float4* lds, double& rel, double& sum, double& mabs,
-                                 double& bad, int& fell_back, int& deferred, int& evals) {
-  NodeTerms T;
-  const int j = node_terms_tab(a, a.free_node[t], T);
-  FastNode F;
-  const float qc = fast_setup(a, T, lds, F);
-  auto qf = [&](float sn, float cs) { return fast_q(F, sn, cs); };
-  const float vin = a.V_in[j];
-  Choice ch;
-  if (kMode == 0) table_search(qf, a, qc, ch);
-  else if (kMode == 1) full_search(qf, a, qc, ch);
-  else if (kMode == 3) evals = walk_search(qf, a, a.walk_from[j], qc, ch);
-  else {
+// ---- nodes whose thrust feet all fall in one cell (one region along v_r and
+// one along v_t; 80-95 % of the nodes of the 96^3 x 64 and 48^4 workloads,
+// whose thrust moves a foot by 0.02-0.05 cell): the four coefficients of the
+// bilinear form stay in registers, 8 corner pairs are gathered instead of 18,
+// and an evaluation is 7 instructions with no region test and no LDS read.
+struct CellNode {
+  float g1, g2, d1, d2;
+  float x, y, z, w;  // Q = x + y dv + z dt + w dv dt
+};
+
+__device__ inline float cell_q(const CellNode& F, float sn, float cs) {
+  const float ov = fmaf(F.g1, sn, F.d1), ot = fmaf(F.g2, cs, F.d2);
+  const float dv = ov - F.d1, dt = ot - F.d2;
+  return fmaf(fmaf(F.w, dt, F.y), dv, fmaf(F.z, dt, F.x));
+}
+
+// Set-up of such a node: the operations of fast_setup on its one region pair,
+// in the same order, so the values are the same bit for bit.  Returns the
+// coast Q.
+__device__ inline float cell_setup(const SweepArgs& a, const NodeTerms& T, const FeetCells& C, CellNode& F) {
+  const Grid& G = a.G;
+  F.g1 = T.g1;
+  F.g2 = T.g2;
+  F.d1 = T.drift[1];
+  F.d2 = T.drift[2];
+  F.x = fmaf(a.P.gamma, a.P.M, a.P.q_thr);
+  F.y = F.z = F.w = 0.0f;
+  float Ic = a.P.M;
+  if (C.ok_r && C.Rv.ok0 && C.Rt.ok0) {
+    const uint32_t s1 = 4u * (uint32_t)G.st[1], s2 = 4u * (uint32_t)G.st[2], so = C.ok_m ? 4u * (uint32_t)G.st[3] : 0u;
+    const uint32_t p = C.plane + __umul24(__umul24(C.Rt.b0, G.n[1]) + C.Rv.b0, s1) + 4u * (uint32_t)C.br;
+    CornerPair lo[4], hi[4];
+#pragma unroll
+    for (int e = 0; e < 4; e++) {
+      const uint32_t o = p + ((e & 1) ? s1 : 0u) + ((e & 2) ? s2 : 0u);
+      lo[e] = pair_at(a.V_in, o);
+      hi[e] = pair_at(a.V_in, o + so);
+    }
+    float W[4], Wc[4];
+#pragma unroll
+    for (int e = 0; e < 4; e++) {
+      const float l = lerp(lo[e].lo, lo[e].hi, C.tr), h = lerp(hi[e].lo, hi[e].hi, C.tr);
+      W[e] = lerp(l, h, C.tm);
+      Wc[e] = C.coast_lo ? l : h;
+    }
+    // local coordinates of the coast foot in the cell
+    const float tv = T.drift[1] - (float)(C.Rv.b0 - T.i[1]);
+    const float tt = T.drift[2] - (float)(C.Rt.b0 - T.i[2]);
+    if (C.ok_m) {
+      const float gam = a.P.gamma;
+      const float cv = W[1] - W[0], ct = W[2] - W[0], dd = (W[3] - W[1]) - (W[2] - W[0]);
+      const float A = lerp(lerp(W[0], W[1], tv), lerp(W[2], W[3], tv), tt);
+      F.x = fmaf(gam, A, a.P.q_thr);
+      F.y = gam * fmaf(dd, tt, cv);
+      F.z = gam * fmaf(dd, tv, ct);
+      F.w = gam * dd;
+    }
+    Ic = lerp(lerp(Wc[0], Wc[1], tv), lerp(Wc[2], Wc[3], tv), tt);
+  }
+  return fmaf(a.P.gamma, Ic, a.P.q_coast);
+}
+
+// The part of the table that can hold its minimum.  On one cell Q(u) = x +
+// b sin u + c cos u + d sin u cos u with b = y g1, c = z g2, d = w g1 g2, so
+// every tabulated Q is x - R cos(u - u*) up to E = |d|/2 plus the rounding of
+// the evaluation, R = hypot(b, c), u* = atan2(b, c) + pi.  The sample nearest
+// to u* lies within pi/K of it, so a sample farther than theta,
+//     1 - cos(theta) = 1 - cos(pi/K) + 2 E / R,
+// is above that one and cannot be the first minimum; the samples within theta are
+// evaluated exactly as the full scan evaluates them.  The number of samples
+// is at most kWindow, else 0 (the caller scans the whole table): nodes with R = 0,
+// non-finite or huge coefficients, and those so flat that the rounding of Q
+// hides the minimum.
+constexpr int kWindow = 24;
+
+__device__ inline int scan_window(const SweepArgs& a, const CellNode& F, int& k0) {
+  k0 = 0;
+  // all coefficients zero (a plateau): every sample has the same Q
+  if (F.y == 0.0f && F.z == 0.0f && F.w == 0.0f) return 1;
+  const float g1 = fabsf(F.g1), g2 = fabsf(F.g2);
+  const float b = F.y * F.g1, c = F.z * F.g2;
+  const float P = fmaf(fabsf(F.w), g2, fabsf(F.y)), Q = fmaf(fabsf(F.w), g1, fabsf(F.z));
+  // the largest |Q|; its unit in the last place bounds the half-units of the two
+  // outer operations, the foot's displacements are half a unit of drift and thrust off each
+  const float top = fmaf(P, g1, fmaf(Q, g2, fabsf(F.x)));
+  const float ulp = __int_as_float(__float_as_int(top) & 0x7f800000) * 1.1920929e-7f;
+  const float E = 1.05f * fmaf(0.5f * fabsf(F.w) * g1, g2,
+                               fmaf(5.9604645e-8f, fmaf(P, fmaf(6.0f, g1, fabsf(F.d1)), Q * fmaf(6.0f, g2, fabsf(F.d2))), ulp));
+  // the approximate root and reciprocals below are within 2e-7 of the exact ones, the
+  // table steps' margin of 0.02 and the 5 % on the rounding bound cover them
+  const float R = __builtin_amdgcn_sqrtf(fmaf(b, b, c * c));
+  // 1 - cos(theta) = 2 s^2 with s = sin(theta / 2); asin(s) <= s + (pi/2 - 1) s^3 on [0, 1]
+  const float h = fmaf(E, __builtin_amdgcn_rcpf(R), 0.5f * a.scan_y0);
+  if (!(R > 1e-18f && R < 1e18f && h <= 1.0f)) return 0;
+  const float s = __builtin_amdgcn_sqrtf(h);
+  const float wid = fmaf(2.0f * a.scan_k, s * fmaf(0.5708f, h, 1.0f), 0.02f);
+  // atan2(b, c) by Abramowitz and Stegun 4.4.49 (error below 1e-5 rad), in table steps:
+  // u* is entry K (atan2(b, c) / (2 pi)) mod K
+  const float ab = fabsf(b), ac = fabsf(c);
+  const float t = fminf(ab, ac) * __builtin_amdgcn_rcpf(fmaxf(ab, ac)), t2 = t * t;
+  float at = t * fmaf(t2, fmaf(t2, fmaf(t2, fmaf(t2, 0.0208351f, -0.0851330f), 0.1801410f), -0.3302995f), 0.9998660f);
+  at = ab > ac ? 1.5707964f - at : at;
+  at = c < 0.0f ? 3.1415927f - at : at;
+  at = b < 0.0f ? -at : at;
+  const float kc = at * a.scan_k;
+  const float lo = ceilf(kc - wid);
+  const int n = (int)(floorf(kc + wid) - lo) + 1;
+  if (n > kWindow || n > a.n_ang) return 0;
+  int k = (int)lo;
+  k = k < 0 ? k + a.n_ang : k;
+  k0 = k >= a.n_ang ? k - a.n_ang : k;
+  return n;
+}
+
+// scan_table for a one-cell node: the window where every active lane of the
+// wave has one (lanes in step through their own windows), else the whole
+// table.  tab: (sin, cos) of the table in LDS.
+__device__ inline void scan_cell(const SweepArgs& a, const CellNode& F, const float2* tab, float& bq, int& bk) {
+  auto qf = [&](float sn, float cs) { return cell_q(F, sn, cs); };
+  int k;
+  const int n = scan_window(a, F, k);
+  if (!__all(n > 0)) {
+    scan_table(qf, a, bq, bk);
+    return;
+  }
+  bq = INFINITY;
+  bk = 0;
+  for (int i = 0; i < n; i++) {
+    const float2 sc = tab[k];
+    const float q = qf(sc.x, sc.y);
+    // the first minimum in table order, also where the window wraps around the table's end
+    if (q < bq || (q == bq && k < bk)) {
+      bq = q;
+      bk = k;
+    }
+    k = k + 1 == a.n_ang ? 0 : k + 1;
+  }
+}
+
+// write_desc for a one-cell node: the cell of every foot is known, and its
+// coordinates are the offsets from it (what axis_cell forms).
+__device__ inline void write_desc_cell(const SweepArgs& a, int t, int j, const NodeTerms& T, const FeetCells& C,
+                                       const Choice& ch) {
+  if (!a.desc_pk && !a.desc16) {
+    write_desc(a, t, j, T, ch);
+    return;
+  }
+  const bool inside = C.ok_r && C.Rv.ok0 && C.Rt.ok0 && (!ch.thr || C.ok_m);
+  const float o1 = ch.thr ? fmaf(T.g1, ch.sn, T.drift[1]) : T.drift[1];
+  const float o2 = ch.thr ? fmaf(T.g2, ch.cs, T.drift[2]) : T.drift[2];
+  const int k1 = C.Rv.b0 - T.i[1], k2 = C.Rt.b0 - T.i[2];
+  const float w1 = inside ? o1 - (float)k1 : 0.0f, w2 = inside ? o2 - (float)k2 : 0.0f;
+  const uint32_t code = (ch.thr ? kDescThr : 0u) | (inside ? (uint32_t)((k1 + 32) | ((k2 + 32) << 6)) : kDescOut);
+  if (a.desc_pk) {
+    a.desc_pk[j] = desc_pack(code, w1, w2);
+    return;
+  }
+  const int k = a.desc_dense ? j : t;
+  a.desc16[k] = (uint16_t)code;
+  a.desc_w[k] = make_float2(w1, w2);
+}
+
+// Sums of a thread over its nodes: residual contributions, seeded fallbacks,
+// thrust evaluations of the table walk.
+struct NodeSums {
+  double rel = 0, sum = 0, mabs = 0, bad = 0;
+  int fell_back = 0, evals = 0;
+};
+
+// Arguments read from memory instead of the kernel's argument block (the
+// batched sweep): by scalar loads, the pointers marked as global memory (the
+// compiler would otherwise have to use flat loads and stores for them).
+typedef const __attribute__((address_space(4))) SweepArgs* ConstArgs;
+template <class P>
+__device__ inline P* in_global(P* p) {
+  return (P*)(__attribute__((address_space(1))) P*)p;
+}
+
+// Search of one node with its set-up done: the choice in ch; false where a
+// seeded node's full search is deferred to the second pass.  kMode: 0
+// tabulated, 1 scan + golden, 2 seeded, 3 table walk.  scan(bq, bk): the
+// table's first minimum.
+template <int kMode, class QF, class Scan>
+__device__ inline bool search_node(const QF& qf, const Scan& scan, const SweepArgs& a, int j, float qc, float vin,
+                                   Choice& ch, NodeSums& S) {
+  float bq;
+  int bk;
+  if (kMode == 0) {
+    scan(bq, bk);
+    table_choice(a, bq, bk, qc, ch);
+  } else if (kMode == 1) {
+    scan(bq, bk);
+    refine_search(qf, a, bq, bk, qc, ch);
+  } else if (kMode == 3) {
+    S.evals += walk_search(qf, a, a.walk_from[j], qc, ch);
+  } else {
     const bool need = seeded_local(qf, a, a.seed[j], qc, vin, ch);
     // A wave where only a few lanes fall back would leave the others idle
     // through a full search: those lanes are listed for a second pass.
     // Where many lanes fall back, the wave does the full search in place.
     const bool few = __popcll(__ballot(need)) <= kDeferLanes;
     if (need) {
-      fell_back = 1;
-      if (a.fb_list && few) {
-        deferred = 1;
-        return;
-      }
-      full_search(qf, a, qc, ch);
+      S.fell_back++;
+      if (a.fb_list && few) return false;
+      scan(bq, bk);
+      refine_search(qf, a, bq, bk, qc, ch);
     }
   }
-  keep_incumbent(qf, a, j, qc, ch);
+  return true;
+}
+
+// Appends the wave's deferred nodes to the second pass's list, one atomic per
+// wave (t: the node's position in sweep_node).
+__device__ inline void defer_nodes(const SweepArgs& a, bool deferred, int t) {
+  const unsigned long long bal = __ballot(deferred);
+  if (!bal) return;
+  const int lane = threadIdx.x & 63, lead = __ffsll((long long)bal) - 1;
+  int base = 0;
+  if (lane == lead) base = atomicAdd(a.fb_count, __popcll(bal));
+  base = __shfl(base, lead, 64);
+  if (deferred) a.fb_list[base + __popcll(bal & ((1ull << lane) - 1ull))] = t;
+}
+
+// Outputs of a node whose choice is made, and its residual contribution.
+__device__ inline void store_node(const SweepArgs& a, int j, float vin, const Choice& ch, bool resid, NodeSums& S) {
   a.V_out[j] = ch.v;
   if (a.pol_ang) a.pol_ang[j] = ch.ang;
   if (a.pol_thr) a.pol_thr[j] = (uint8_t)ch.thr;
-  if (a.desc_code || a.desc16 || a.desc_pk) write_desc(a, t, j, T, ch);
-  node_residual(vin, ch.v, rel, sum, mabs, bad);
+  if (resid) node_residual(vin, ch.v, S.rel, S.sum, S.mabs, S.bad);
+}
+
+// One free node of a sweep on the factorised path.  kOne: its thrust feet
+// share one cell.  lds: 4 * blockDim.x float4 (general form); tab: (sin, cos)
+// of the table (one-cell form).
+template <int kMode, bool kOne>
+__device__ inline void fast_node(const SweepArgs& a, int t, uint32_t packed, float4* lds, const float2* tab, bool resid,
+                                 NodeSums& S) {
+  NodeTerms T;
+  const int j = node_terms_tab(a, packed, T);
+  const float vin = (resid || kMode == 2) ? a.V_in[j] : 0.0f;
+  FeetCells C;
+  feet_cells<kOne>(a, T, C);
+  typename std::conditional<kOne, CellNode, FastNode>::type F;
+  float qc;
+  if constexpr (kOne) qc = cell_setup(a, T, C, F);
+  else qc = fast_setup(a, T, C, lds, F);
+  auto qf = [&](float sn, float cs) {
+    if constexpr (kOne) return cell_q(F, sn, cs);
+    else return fast_q(F, sn, cs);
+  };
+  auto scan = [&](float& bq, int& bk) {
+    if constexpr (kOne && kMode != 0) scan_cell(a, F, tab, bq, bk);
+    else scan_table(qf, a, bq, bk);
+  };
+  Choice ch;
+  const bool done = search_node<kMode>(qf, scan, a, j, qc, vin, ch, S);
+  if (kMode == 2 && a.fb_list) defer_nodes(a, !done, t);
+  if (!done) return;
+  keep_incumbent(qf, a, j, qc, ch);
+  if (a.desc_code || a.desc16 || a.desc_pk) {
+    // formats by free-list position: the node's place in node order
+    const int at = a.desc_pk ? 0 : (t & ~(kOrderChunk - 1)) + a.sweep_pos[t];
+    if (kOne) write_desc_cell(a, at, j, T, C, ch);
+    else write_desc(a, at, j, T, ch);
+  }
+  store_node(a, j, vin, ch, resid, S);
+}
+
+// A workgroup's nodes, one per thread.  A wave whose nodes are all one-cell
+// nodes (sweep_node keeps the two kinds apart, see k_order_free) takes the
+// short form, any other the general one.  Vector instruction issue bounds the
+// sweep with many controls (96^3 x 64, coast + scan 64 + golden 12, value
+// iteration: 1.99 -> 1.45 ms a sweep with the two forms, the scan's window and
+// the tables of the node terms; 2212 -> 1570 vector instructions per wave),
+// and the latency of its loads the one with few (40^4, 17 controls: 713 -> 470
+// instructions per wave, 1.2 times as fast).  Splitting the nodes inside
+// the kernel instead (listing the others in LDS, per workgroup or per wave, and
+// running them together) took 1.96-2.8 ms: the second phase leaves lanes and
+// waves idle.
+template <int kMode>
+__device__ inline void sweep_nodes(const SweepArgs& a, int tile, float4* lds, bool resid, NodeSums& S) {
+  const int bd = (int)blockDim.x, tid = (int)threadIdx.x;
+  const int first = __builtin_amdgcn_readfirstlane(tile * bd + (tid & ~63));
+  const int t = first + (tid & 63), in_wave = min(64, a.n_free - first);
+  // the node, the kind of its wave and the table are loaded together: a
+  // sweep of few controls waits on memory, not on arithmetic
+  const uint32_t packed = t < a.n_free ? a.sweep_node[t] : 0u;
+  const bool one = in_wave > 0 && (first & (kOrderChunk - 1)) + in_wave <= a.one_cell[first / kOrderChunk];
+  float2* tab = reinterpret_cast<float2*>(lds + 4 * bd);
+  if (kMode == 1 || kMode == 2) {
+    for (int k = tid; k < a.n_ang; k += bd) tab[k] = make_float2(a.tab_sin[k], a.tab_cos[k]);
+    __syncthreads();
+  }
+  if (t >= a.n_free) return;
+  if (one) fast_node<kMode, true>(a, t, packed, lds, tab, resid, S);
+  else fast_node<kMode, false>(a, t, packed, lds, tab, resid, S);
+}
+
+// Dynamic LDS of sweep_nodes.
+inline size_t sweep_lds_bytes(int block, int n_ang) {
+  return sizeof(float4) * 4 * (size_t)block + sizeof(float2) * (size_t)n_ang;
 }
 
 }  // namespace dpo
