@@ -159,10 +159,6 @@ hipStream_t S(void* s) { return reinterpret_cast<hipStream_t>(s); }
 
 constexpr int kRot = 2 + 2 * 64;
 
-// Workgroups of the second (fallback) pass of a seeded sweep; the residual
-// partial buffer has room for them after the first pass's.
-constexpr int kFallbackBlocks = 2048;
-
 // MI355X Infinity Cache (last-level cache shared by the XCDs).
 constexpr double kLastLevelCacheBytes = 256.0 * 1024 * 1024;
 
@@ -642,21 +638,19 @@ int sweep_seeded(dpo_ctx* c, const float* Vin, float* Vout, float* ang, uint8_t*
   }
   // factorised path: the local searches first, then the full search at the
   // nodes that fall back, as a second launch over the list the first built
-  if (!c->fb_list) {
-    if (hipMalloc(&c->fb_list, sizeof(int) * (size_t)c->n_free) != hipSuccess ||
-        hipMalloc(&c->fb_count, sizeof(int)) != hipSuccess)
-      return fail(c, DPO_ENOMEM, "fallback list alloc");
-  }
+  const size_t segs = (size_t)blocks_for(c->n_free, 64);
+  if ((!c->fb_list && hipMalloc(&c->fb_list, sizeof(int) * kDeferLanes * segs) != hipSuccess) ||
+      (!c->fb_count && hipMalloc(&c->fb_count, sizeof(int) * segs) != hipSuccess))
+    return fail(c, DPO_ENOMEM, "fallback list alloc");
   a.fb_list = c->fb_list;
   a.fb_count = c->fb_count;
   const int nb1 = blocks_for(c->n_free, c->block);
-  const int nb2 = std::min(kFallbackBlocks, nb1);
-  hipError_t e = launch_zero_count(c->fb_count, s);
-  if (e == hipSuccess) e = launch_sweep_fast(a, 2, c->block, s);
+  const int nb2 = fallback_blocks(c->n_free, c->block);
+  hipError_t e = launch_sweep_fast(a, 2, c->block, s);
   if (e == hipSuccess) {
     SweepArgs b = a;
     b.partial = c->partial + (size_t)kPartial * nb1;
-    e = launch_sweep_fallback(b, c->block, nb2, s);
+    e = launch_sweep_fallback(b, c->block, s);
   }
   c->last_blocks = nb1 + nb2;
   if (e != hipSuccess) return hip_fail(c, e, "seeded sweep launch");
@@ -1003,7 +997,7 @@ int dpo_create(const dpo_grid* grid, const dpo_problem* prob, const dpo_search* 
       return cleanup(DPO_EHIP);
     }
   }
-  c->partial_blocks = blocks_for(total > 0 ? total : 1, 64) + kFallbackBlocks;
+  c->partial_blocks = blocks_for(total > 0 ? total : 1, 64) + fallback_blocks(total > 0 ? total : 1, 64);
   // the partials, then the first stage of their reduction
   if (hipMalloc(&c->partial, sizeof(double) * kPartial * (c->partial_blocks + kResidStage)) != hipSuccess) {
     c->err = "device allocation failed in dpo_create";

@@ -289,18 +289,44 @@ __global__ __launch_bounds__(kMaxBlock) __attribute__((amdgpu_waves_per_eu(8))) 
 
 // Second pass of the seeded sweep: the full search at the nodes the first
 // pass listed, so that a wave's full searches run together instead of
-// stalling the lanes whose local search sufficed.  Persistent grid over the
-// list; the residual partials of this pass follow those of the first.
+// stalling the lanes whose local search sufficed.  A wave packs the lists of
+// kFallbackSegs waves of the first pass into full waves of its own (entry e
+// of their sequence by a search in the running counts).  The residual partials
+// of this pass follow those of the first.
 __global__ __launch_bounds__(kMaxBlock) __attribute__((amdgpu_waves_per_eu(8))) void k_sweep_fallback(SweepArgs a) {
   extern __shared__ float4 dyn_lds[];
+<<<<<<< Updated upstream
   const int count = *a.fb_count;
   NodeSums S;
   for (int k = blockIdx.x * blockDim.x + threadIdx.x; k < count; k += gridDim.x * blockDim.x)
     fast_node<1, false>(a, a.fb_list[k], a.sweep_node[a.fb_list[k]], dyn_lds, nullptr, true, S);
+=======
+  __shared__ int before[kMaxBlock / 64][kFallbackSegs + 1];
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int segs = (a.n_free + 63) >> 6;
+  const int first = (blockIdx.x * (int)(blockDim.x >> 6) + wave) * kFallbackSegs;
+  int sum = lane < kFallbackSegs && first + lane < segs ? a.fb_count[first + lane] : 0;
+#pragma unroll
+  for (int o = 1; o < kFallbackSegs; o <<= 1) {
+    const int up = __shfl_up(sum, o, 64);
+    if (lane >= o) sum += up;
+  }
+  if (lane < kFallbackSegs) before[wave][lane + 1] = sum;
+  if (lane == 0) before[wave][0] = 0;
+  const int total = __shfl(sum, kFallbackSegs - 1, 64);
+  __syncthreads();
+  NodeSums S;
+  for (int e = lane; e < total; e += 64) {
+    int q = 0;
+#pragma unroll
+    for (int h = kFallbackSegs / 2; h > 0; h >>= 1)
+      if (before[wave][q + h] <= e) q += h;
+    const int t = a.fb_list[(first + q) * kDeferLanes + e - before[wave][q]];
+    fast_node<1, false>(a, t, a.sweep_node[t], dyn_lds, nullptr, true, S);
+  }
+>>>>>>> Stashed changes
   block_residual(S.rel, S.sum, S.mabs, S.bad, 0.0, a.partial, blockIdx.x);
 }
-
-__global__ void k_zero_count(int* count) { *count = 0; }
 
 // Frozen-policy sweep (eq:p_eval applied once).  The residual reduction is
 // only compiled in when a caller asks for it; the policy-iteration loop does
@@ -895,11 +921,17 @@ hipError_t launch_sweep_fast(const SweepArgs& a, int mode, int block, hipStream_
   return hipGetLastError();
 }
 
-hipError_t launch_zero_count(int* count, hipStream_t s) { DPO_LAUNCH(k_zero_count, 1, 1, s, count); }
+int fallback_blocks(long long n, int block) { return blocks_for(n, block * kFallbackSegs); }
 
+<<<<<<< Updated upstream
 hipError_t launch_sweep_fallback(const SweepArgs& a, int block, int blocks, hipStream_t s) {
   const size_t lds = sweep_lds_bytes(block, a.n_ang);
   hipLaunchKernelGGL(k_sweep_fallback, dim3(blocks), dim3(block), lds, s, a);
+=======
+hipError_t launch_sweep_fallback(const SweepArgs& a, int block, hipStream_t s) {
+  const size_t lds = sizeof(float4) * 4 * (size_t)block;
+  hipLaunchKernelGGL(k_sweep_fallback, dim3(fallback_blocks(a.n_free, block)), dim3(block), lds, s, a);
+>>>>>>> Stashed changes
   return hipGetLastError();
 }
 
