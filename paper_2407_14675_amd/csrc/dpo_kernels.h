@@ -88,14 +88,11 @@ struct SweepArgs {
   double w_time, w_fuel, lambda;
 };
 
-<<<<<<< Updated upstream
-=======
 // At most this many fallback lanes of a wave are deferred to the second pass,
 // whose waves take the lists of kFallbackSegs waves each.
 constexpr int kDeferLanes = 16;
 constexpr int kFallbackSegs = 32;
 
->>>>>>> Stashed changes
 constexpr int kOrderChunk = 4096;  // entries of the free list ordered together (a multiple of 64)
 
 inline int blocks_for(long long n, int per = kBlock) { return (int)((n + per - 1) / per); }

@@ -295,12 +295,6 @@ __global__ __launch_bounds__(kMaxBlock) __attribute__((amdgpu_waves_per_eu(8))) 
 // of this pass follow those of the first.
 __global__ __launch_bounds__(kMaxBlock) __attribute__((amdgpu_waves_per_eu(8))) void k_sweep_fallback(SweepArgs a) {
   extern __shared__ float4 dyn_lds[];
-<<<<<<< Updated upstream
-  const int count = *a.fb_count;
-  NodeSums S;
-  for (int k = blockIdx.x * blockDim.x + threadIdx.x; k < count; k += gridDim.x * blockDim.x)
-    fast_node<1, false>(a, a.fb_list[k], a.sweep_node[a.fb_list[k]], dyn_lds, nullptr, true, S);
-=======
   __shared__ int before[kMaxBlock / 64][kFallbackSegs + 1];
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int segs = (a.n_free + 63) >> 6;
@@ -324,7 +318,6 @@ __global__ __launch_bounds__(kMaxBlock) __attribute__((amdgpu_waves_per_eu(8))) 
     const int t = a.fb_list[(first + q) * kDeferLanes + e - before[wave][q]];
     fast_node<1, false>(a, t, a.sweep_node[t], dyn_lds, nullptr, true, S);
   }
->>>>>>> Stashed changes
   block_residual(S.rel, S.sum, S.mabs, S.bad, 0.0, a.partial, blockIdx.x);
 }
 
@@ -923,15 +916,9 @@ hipError_t launch_sweep_fast(const SweepArgs& a, int mode, int block, hipStream_
 
 int fallback_blocks(long long n, int block) { return blocks_for(n, block * kFallbackSegs); }
 
-<<<<<<< Updated upstream
-hipError_t launch_sweep_fallback(const SweepArgs& a, int block, int blocks, hipStream_t s) {
-  const size_t lds = sweep_lds_bytes(block, a.n_ang);
-  hipLaunchKernelGGL(k_sweep_fallback, dim3(blocks), dim3(block), lds, s, a);
-=======
 hipError_t launch_sweep_fallback(const SweepArgs& a, int block, hipStream_t s) {
   const size_t lds = sizeof(float4) * 4 * (size_t)block;
   hipLaunchKernelGGL(k_sweep_fallback, dim3(fallback_blocks(a.n_free, block)), dim3(block), lds, s, a);
->>>>>>> Stashed changes
   return hipGetLastError();
 }
 

@@ -832,18 +832,6 @@ __device__ inline bool search_node(const QF& qf, const Scan& scan, const SweepAr
   return true;
 }
 
-<<<<<<< Updated upstream
-// Appends the wave's deferred nodes to the second pass's list, one atomic per
-// wave (t: the node's position in sweep_node).
-__device__ inline void defer_nodes(const SweepArgs& a, bool deferred, int t) {
-  const unsigned long long bal = __ballot(deferred);
-  if (!bal) return;
-  const int lane = threadIdx.x & 63, lead = __ffsll((long long)bal) - 1;
-  int base = 0;
-  if (lane == lead) base = atomicAdd(a.fb_count, __popcll(bal));
-  base = __shfl(base, lead, 64);
-  if (deferred) a.fb_list[base + __popcll(bal & ((1ull << lane) - 1ull))] = t;
-=======
 // Lists the wave's deferred nodes for the second pass, in node order: each
 // wave of 64 nodes has its own kDeferLanes entries and its own count, so no two
 // waves meet (one atomic per wave on a shared count took as long as the sweep
@@ -853,7 +841,6 @@ __device__ inline void defer_nodes(const SweepArgs& a, bool deferred, int t) {
   const int lane = threadIdx.x & 63, seg = t >> 6;
   if (lane == __ffsll((long long)here) - 1) a.fb_count[seg] = __popcll(bal);
   if (deferred) a.fb_list[seg * kDeferLanes + __popcll(bal & ((1ull << lane) - 1ull))] = t;
->>>>>>> Stashed changes
 }
 
 // Outputs of a node whose choice is made, and its residual contribution.
