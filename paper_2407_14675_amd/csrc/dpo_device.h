@@ -208,28 +208,26 @@ __device__ inline float cell_value(const float* __restrict__ p, const Grid& G, c
   return lerp(e0, e1, t[3]);
 }
 
-// The 16 corners of the cell a node's last evaluation read, kept in
-// registers: the feet of one node's controls mostly share a cell (on the
-// crown problem a step moves a foot by less than a tenth of a cell), so a
-// search reloads the corners only when the cell changes.  key: offset of the
-// cell's lowest corner in V (-1 = empty); the lerps are cell_value's, in the
-// same order, so the value is the same bit for bit.
+// Smallest float above x (x finite; 0 maps to the smallest normal float).
+__device__ inline float next_up(float x) {
+  if (x == 0.0f) return 1.17549435e-38f;
+  return __int_as_float(__float_as_int(x) + (x > 0.0f ? 1 : -1));
+}
+
+// The cell a node's last evaluation fell in, kept in registers with its 16
+// corners: the feet of one node's controls mostly share a cell (on the crown
+// problem a step moves a foot by less than a tenth of a cell), so a search
+// finds the cell and loads the corners only when a foot leaves it.  f: the
+// cell's base minus the node, per axis (NaN: no cell yet, and every foot is
+// looked up); wrap: what the periodic axis subtracts; top1, top2: the largest
+// cell coordinate along v_r and v_t that is still in the cell (1 in the last
+// cell, whose upper face is part of it).
 struct CornerCache {
-  int key;
+  float f[4], wrap, top1, top2;
   CornerPair v[8];
 };
 
-__device__ inline float cell_value_cached(const float* __restrict__ V, const Grid& G, int key, const float t[4], int s3,
-                                          CornerCache& cc) {
-  if (key != cc.key) {
-    const int s1 = G.st[1], s2 = G.st[2];
-#pragma unroll
-    for (int e = 0; e < 8; e++) {
-      const int o = ((e & 1) ? s1 : 0) + ((e & 2) ? s2 : 0) + ((e & 4) ? s3 : 0);
-      cc.v[e] = *reinterpret_cast<const CornerPair*>(V + key + o);
-    }
-    cc.key = key;
-  }
+__device__ inline float cached_value(const CornerCache& cc, const float t[4]) {
   float c[8];
 #pragma unroll
   for (int e = 0; e < 8; e++) c[e] = lerp(cc.v[e].lo, cc.v[e].hi, t[0]);
@@ -240,6 +238,58 @@ __device__ inline float cell_value_cached(const float* __restrict__ V, const Gri
   const float e0 = lerp(d0, d1, t[2]);
   const float e1 = lerp(d2, d3, t[2]);
   return lerp(e0, e1, t[3]);
+}
+
+// I[V] at the foot i + off through the cache.  A foot inside the cached cell
+// takes the coordinates foot_cell would form by the same subtractions (0 <= t
+// < 1 on an axis means that floor(off) is the cached one); any other is looked
+// up by foot_cell, whatever its arrangement.  Along the periodic axis a foot
+// within 2e-5 of the cell's upper face is looked up too (there the wrap's
+// quotient may round up).
+template <bool kCrown>
+__device__ inline float cached_interp(const float* __restrict__ V, const Grid& G, const int i[4], const float off[4],
+                                      float M, CornerCache& cc) {
+  float o1 = off[1], o2 = off[2];
+  if (kCrown) {
+    o1 = fminf(fmaxf(o1, (float)(-i[1])), (float)(G.n[1] - 1 - i[1]));
+    o2 = fminf(fmaxf(o2, (float)(-i[2])), (float)(G.n[2] - 1 - i[2]));
+  }
+  float t[4];
+  t[0] = off[0] - cc.f[0];
+  t[1] = o1 - cc.f[1];
+  t[2] = o2 - cc.f[2];
+  constexpr float near_top = kCrown ? 2e-5f : 0.0f;
+  if (kCrown) t[3] = (((float)i[3] + off[3]) - cc.wrap) - cc.f[3];
+  else t[3] = off[3] - cc.f[3];
+  const float low = fminf(fminf(t[0], t[1]), fminf(t[2], t[3]));
+  const bool in = low >= 0.0f && fmaxf(t[0], t[3] + near_top) < 1.0f && o1 < cc.top1 && o2 < cc.top2;
+  if (!in) {
+    // leaving the domain along r: the same answer for every control of most such nodes
+    if (!(off[0] >= (float)(-i[0]) && off[0] <= (float)(G.n[0] - 1 - i[0]))) return M;
+    int base[4];
+    if (!foot_cell(G, i, off, base, t)) return M;
+    const int s3 = (kCrown && base[3] == G.n[3] - 1) ? -base[3] * G.st[3] : G.st[3];
+    const float* p = V + (base[0] + base[1] * G.st[1] + base[2] * G.st[2] + base[3] * G.st[3]);
+#pragma unroll
+    for (int e = 0; e < 8; e++) {
+      const int o = ((e & 1) ? G.st[1] : 0) + ((e & 2) ? G.st[2] : 0) + ((e & 4) ? s3 : 0);
+      cc.v[e] = *reinterpret_cast<const CornerPair*>(p + o);
+    }
+    if (!(cc.wrap == cc.wrap)) return cached_value(cc, t);  // not to be kept (see cache_init)
+    cc.f[0] = (float)(base[0] - i[0]);
+    cc.f[1] = (float)(base[1] - i[1]);
+    cc.f[2] = (float)(base[2] - i[2]);
+    cc.top1 = base[1] == G.n[1] - 2 ? next_up(cc.f[1] + 1.0f) : cc.f[1] + 1.0f;
+    cc.top2 = base[2] == G.n[2] - 2 ? next_up(cc.f[2] + 1.0f) : cc.f[2] + 1.0f;
+    if (kCrown) {
+      const float nf = (float)G.n[3];
+      cc.wrap = nf * floorf(((float)i[3] + off[3]) / nf);
+      cc.f[3] = (float)base[3];
+    } else {
+      cc.f[3] = (float)(base[3] - i[3]);
+    }
+  }
+  return cached_value(cc, t);
 }
 
 // Q1 interpolation of V at s = i + off (paper Section 3: multilinear I[V],
@@ -299,8 +349,10 @@ __device__ inline void heun_terms(const Grid& G, const Phys& P, const double x[4
 
 // (tau/2)*(b(x~) - b(x)) in cells along r, v_r, v_t and axis 3 (the mass:
 // zero, its rate is constant; the crown's theta: v_t~/r~ - v_t/r).
+// kCrown: the crown problem, whose mass is constant.
+template <bool kCrown = false>
 __device__ inline void heun_corr(const HeunTerms& H, int thr, float sn, float cs, float c[4]) {
-  if (!H.orbit) {
+  if (!kCrown && !H.orbit) {
     c[0] = c[1] = c[2] = c[3] = 0.0f;
     return;
   }
@@ -314,8 +366,9 @@ __device__ inline void heun_corr(const HeunTerms& H, int thr, float sn, float cs
   const float grav = H.mu * dr * (2.0f * H.r + dr) * inv * inv;
   // -(v_r~ v_t~/r~ - v_r v_t/r)
   const float cor = -((dv * H.vt + H.vr * dw + dv * dw) * H.r - H.vr * H.vt * dr) * inv;
-  float tv = 0.0f, tt = 0.0f;
-  if (thr) {
+  // crown: H.mdot is 0; added all the same, so that the sums round as the general form's
+  float tv = kCrown ? H.mdot : 0.0f, tt = tv;
+  if (!kCrown && thr) {
     const float dm = -H.tau * H.mdot;
     const float dinv_m = -dm / (H.m * (H.m + dm));  // 1/m~ - 1/m
     tv = H.accel * sn * dinv_m;
@@ -324,11 +377,11 @@ __device__ inline void heun_corr(const HeunTerms& H, int thr, float sn, float cs
   c[0] = H.sc[0] * dv;
   c[1] = H.sc[1] * (cent + grav + tv);
   c[2] = H.sc[2] * (cor + tt);
-  c[3] = H.crown ? H.sc[3] * ((dw * H.r - H.vt * dr) * inv) : 0.0f;
+  c[3] = kCrown || H.crown ? H.sc[3] * ((dw * H.r - H.vt * dr) * inv) : 0.0f;
 }
 
 // Foot displacement (cells) of a control under the node's integrator.
-template <bool kHeun>
+template <bool kHeun, bool kCrown = false>
 __device__ inline void foot_off(const NodeTerms& T, const HeunTerms& H, int thr, float sn, float cs, float off[4]) {
   off[0] = T.drift[0];
   off[1] = thr ? fmaf(T.g1, sn, T.drift[1]) : T.drift[1];
@@ -336,11 +389,15 @@ __device__ inline void foot_off(const NodeTerms& T, const HeunTerms& H, int thr,
   off[3] = T.drift[3] + (thr ? T.gm : 0.0f);
   if (kHeun) {
     float c[4];
-    heun_corr(H, thr, sn, cs, c);
-    off[0] += c[0];
-    off[1] += c[1];
-    off[2] += c[2];
-    off[3] += c[3];
+    heun_corr<kCrown>(H, thr, sn, cs, c);
+    // the sums rounded on their own in every form of the sweeps, whatever the compiler could fuse
+    {
+#pragma clang fp contract(off)
+      off[0] += c[0];
+      off[1] += c[1];
+      off[2] += c[2];
+      off[3] += c[3];
+    }
   }
 }
 
@@ -355,21 +412,33 @@ __device__ inline float q_step(const float* __restrict__ V, const Grid& G, const
   return fmaf(P.gamma, interp_off<kSnap>(V, G, T.i, off, P.M), (thr ? P.q_thr : P.q_coast) + qx);
 }
 
-// q_step through a node's corner cache (the cell's corners are loaded only
-// when the foot leaves the cell of the previous evaluation).
-template <bool kHeun>
+// An empty cache.  keep: cells may be kept (every displacement of the node is
+// finite and moderate, so the fast test cannot be fooled by a NaN that the
+// face clamp would hide).
+__device__ inline void cache_init(const NodeTerms& T, const HeunTerms& H, bool heun, CornerCache& cc) {
+  const float big = 1e6f;
+  bool keep = true;
+  for (int k = 0; k < 4; k++) keep = keep && fabsf(T.drift[k]) < big;
+  keep = keep && fabsf(T.g1) < big && fabsf(T.g2) < big && fabsf(T.gm) < big;
+  if (heun && H.orbit) {
+    const float rr = H.r * (H.r + H.tau * H.vr);
+    keep = keep && fabsf(H.r) < big && fabsf(H.vr) < big && fabsf(H.vt) < big && fabsf(H.d1) < big &&
+           fabsf(H.d2) < big && fabsf(H.acc) < big && fabsf(H.tau) < big && fabsf(H.mu) < big && fabsf(H.accel) < big &&
+           fabsf(rr) > 1e-6f && fabsf(H.m * (H.m - H.tau * H.mdot)) > 1e-6f && fabsf(H.m) < big && fabsf(H.mdot) < big;
+    for (int k = 0; k < 4; k++) keep = keep && fabsf(H.sc[k]) < big;
+  }
+  for (int k = 0; k < 4; k++) cc.f[k] = NAN;
+  cc.wrap = keep ? 0.0f : NAN;
+  cc.top1 = cc.top2 = 0.0f;
+}
+
+// q_step through a node's cache.
+template <bool kHeun, bool kCrown>
 __device__ inline float q_step_cached(const float* __restrict__ V, const Grid& G, const Phys& P, const NodeTerms& T,
                                       const HeunTerms& H, int thr, float sn, float cs, float qx, CornerCache& cc) {
   float off[4];
-  foot_off<kHeun>(T, H, thr, sn, cs, off);
-  int base[4];
-  float t[4];
-  float I = P.M;
-  if (foot_cell(G, T.i, off, base, t)) {
-    const int s3 = (G.periodic3 && base[3] == G.n[3] - 1) ? -base[3] * G.st[3] : G.st[3];
-    I = cell_value_cached(V, G, base[0] + base[1] * G.st[1] + base[2] * G.st[2] + base[3] * G.st[3], t, s3, cc);
-  }
-  return fmaf(P.gamma, I, (thr ? P.q_thr : P.q_coast) + qx);
+  foot_off<kHeun, kCrown>(T, H, thr, sn, cs, off);
+  return fmaf(P.gamma, cached_interp<kCrown>(V, G, T.i, off, P.M, cc), (thr ? P.q_thr : P.q_coast) + qx);
 }
 
 // The crown problem's orbital-element running cost at a physical state x =

@@ -153,6 +153,15 @@ __global__ __launch_bounds__(kBlock) void k_node_tables(SweepArgs a, const float
   }
 }
 
+// Heun terms of a free node from its packed coordinates (grid coordinates
+// formed as lo + i*h, the product rounded before the sum).
+__device__ inline void node_heun(const SweepArgs& a, const int i[4], HeunTerms& H) {
+#pragma clang fp contract(off)
+  double x[4];
+  for (int k = 0; k < 4; k++) x[k] = a.G.lo[k] + (double)i[k] * a.G.h[k];
+  heun_terms(a.G, a.P, x, a.P.dt, H);
+}
+
 // Order of the free list for the factorised sweeps.  Whether a node's thrust
 // feet share one cell depends on the grid and the physics alone, and the 64
 // consecutive nodes of a wave nearly always hold one whose feet do not (95 %
@@ -224,21 +233,18 @@ __global__ __launch_bounds__(kBlock) void k_init_value(const uint8_t* __restrict
 }
 
 // --------------------------------------------------------------- a2..a8
-// Heun terms of a free node from its packed coordinates (grid coordinates
-// formed as lo + i*h, the product rounded before the sum).
-__device__ inline void node_heun(const SweepArgs& a, const int i[4], HeunTerms& H) {
-#pragma clang fp contract(off)
-  double x[4];
-  for (int k = 0; k < 4; k++) x[k] = a.G.lo[k] + (double)i[k] * a.G.h[k];
-  heun_terms(a.G, a.P, x, a.P.dt, H);
-}
-
-// ---- direct path: every evaluation forms its foot and cell; the 16 corners
-// come from V when the cell differs from the previous evaluation's (a
-// per-node corner cache).  Used for any problem and for the Heun foot; the
-// fast path below covers the orbit workloads with the Euler foot.
-template <int kMode, bool kHeun>
-__global__ __launch_bounds__(kBlock) void k_sweep_direct(SweepArgs a) {
+// ---- direct path: every evaluation forms its foot; cell and corners come
+// from the node's cache unless the foot leaves the cell of the previous
+// evaluation (CornerCache).  Used for any problem and for the Heun foot; the
+// fast path below covers the orbit workloads with the Euler foot.  Bound by
+// vector instruction issue: looking every foot's cell up (four axes with
+// their faces, the periodic one with a division) was half of the instructions.
+// Example 1 (110 x 30 x 30 x 30, 73 controls, Heun foot): 589 -> 389 us, 11,200
+// -> 6,600 vector instructions per wave; five waves per SIMD at 96 registers (four at 108:
+// 408 us, six with spills: 0.7 ms).  Ordering the nodes as for the factorised
+// sweeps took 414 us: too few nodes here have feet in several cells.
+template <int kMode, bool kHeun, bool kCrown>
+__global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(5))) void k_sweep_direct(SweepArgs a) {
   const int tile = xcd_tile(blockIdx.x, gridDim.x);
   const int t = tile * kBlock + threadIdx.x;
   double rel = 0, sum = 0, mabs = 0, bad = 0;
@@ -251,15 +257,17 @@ __global__ __launch_bounds__(kBlock) void k_sweep_direct(SweepArgs a) {
     const float* __restrict__ V = a.V_in;
     const float qx = a.qnode ? a.qnode[j] : 0.0f;
     CornerCache cc;
-    cc.key = -1;
-    auto qf = [&](float sn, float cs) { return q_step_cached<kHeun>(V, a.G, a.P, T, H, 1, sn, cs, qx, cc); };
-    const float qc = q_step_cached<kHeun>(V, a.G, a.P, T, H, 0, 0.0f, 1.0f, qx, cc);
+    cache_init(T, H, kHeun, cc);
+    auto qf = [&](float sn, float cs) { return q_step_cached<kHeun, kCrown>(V, a.G, a.P, T, H, 1, sn, cs, qx, cc); };
+    const float qc = q_step_cached<kHeun, kCrown>(V, a.G, a.P, T, H, 0, 0.0f, 1.0f, qx, cc);
     const float vin = V[j];
     Choice ch;
-    if (kMode == 0) table_search(qf, a, qc, ch);
-    else if (kMode == 1) full_search(qf, a, qc, ch);
+    // two evaluations in flight: eight copies of the look-up outgrow the instruction cache
+    constexpr int kUnroll = 2;
+    if (kMode == 0) table_search<false, kUnroll>(qf, a, qc, ch);
+    else if (kMode == 1) full_search<false, kUnroll>(qf, a, qc, ch);
     else if (kMode == 3) evals = walk_search(qf, a, a.walk_from[j], qc, ch);
-    else fell_back = seeded_search(qf, a, a.seed[j], qc, vin, ch);
+    else fell_back = seeded_search<kUnroll>(qf, a, a.seed[j], qc, vin, ch);
     keep_incumbent(qf, a, j, qc, ch);
     a.V_out[j] = ch.v;
     if (a.pol_ang) a.pol_ang[j] = ch.ang;
@@ -882,18 +890,20 @@ hipError_t launch_init_value(const uint8_t* kind, float M, float* V, int N, hipS
   DPO_LAUNCH(k_init_value, blocks_for(N), kBlock, s, kind, M, V, N);
 }
 
-hipError_t launch_sweep_direct(const SweepArgs& a, int mode, hipStream_t s) {
+namespace {
+template <bool kHeun, bool kCrown>
+hipError_t sweep_direct(const SweepArgs& a, int mode, hipStream_t s) {
   const int nb = blocks_for(a.n_free);
-  if (a.P.heun) {
-    if (mode == 0) DPO_LAUNCH((k_sweep_direct<0, true>), nb, kBlock, s, a);
-    if (mode == 1) DPO_LAUNCH((k_sweep_direct<1, true>), nb, kBlock, s, a);
-    if (mode == 2) DPO_LAUNCH((k_sweep_direct<2, true>), nb, kBlock, s, a);
-    DPO_LAUNCH((k_sweep_direct<3, true>), nb, kBlock, s, a);
-  }
-  if (mode == 0) DPO_LAUNCH((k_sweep_direct<0, false>), nb, kBlock, s, a);
-  if (mode == 1) DPO_LAUNCH((k_sweep_direct<1, false>), nb, kBlock, s, a);
-  if (mode == 2) DPO_LAUNCH((k_sweep_direct<2, false>), nb, kBlock, s, a);
-  DPO_LAUNCH((k_sweep_direct<3, false>), nb, kBlock, s, a);
+  if (mode == 0) DPO_LAUNCH((k_sweep_direct<0, kHeun, kCrown>), nb, kBlock, s, a);
+  if (mode == 1) DPO_LAUNCH((k_sweep_direct<1, kHeun, kCrown>), nb, kBlock, s, a);
+  if (mode == 2) DPO_LAUNCH((k_sweep_direct<2, kHeun, kCrown>), nb, kBlock, s, a);
+  DPO_LAUNCH((k_sweep_direct<3, kHeun, kCrown>), nb, kBlock, s, a);
+}
+}  // namespace
+
+hipError_t launch_sweep_direct(const SweepArgs& a, int mode, hipStream_t s) {
+  if (a.P.model == 2) return a.P.heun ? sweep_direct<true, true>(a, mode, s) : sweep_direct<false, true>(a, mode, s);
+  return a.P.heun ? sweep_direct<true, false>(a, mode, s) : sweep_direct<false, false>(a, mode, s);
 }
 
 hipError_t launch_node_cost(const Grid& G, const Phys& P, float* qnode, int N, hipStream_t s) {

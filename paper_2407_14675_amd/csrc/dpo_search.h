@@ -158,13 +158,14 @@ __device__ inline void golden(const QF& qf, float s0, float c0, float half, int 
 // minimum (entries whose Q is not below +inf are never taken, and with none
 // taken the index is 0, as in the one-lane pass).  Every lane ends with the
 // result; the caller's lanes must all be active.
-template <bool kWave = false, class QF>
+// kUnroll: evaluations in flight per lane.
+template <bool kWave = false, int kUnroll = 8, class QF>
 __device__ inline void scan_table(const QF& qf, const SweepArgs& a, float& bq, int& bk) {
   bq = INFINITY;
   bk = 0;
   if (!kWave) {
     const ConstTable ts = const_table(a.tab_sin), tc = const_table(a.tab_cos);
-#pragma unroll 8
+#pragma unroll kUnroll
     for (int k = 0; k < a.n_ang; k++) {
       const float q = qf(ts[k], tc[k]);
       if (q < bq) {
@@ -214,11 +215,11 @@ __device__ inline void refine_search(const QF& qf, const SweepArgs& a, float bq,
   ch.cs = g.best_c;
 }
 
-template <bool kWave = false, class QF>
+template <bool kWave = false, int kUnroll = 8, class QF>
 __device__ inline void full_search(const QF& qf, const SweepArgs& a, float qc, Choice& ch) {
   float bq;
   int bk;
-  scan_table<kWave>(qf, a, bq, bk);
+  scan_table<kWave, kUnroll>(qf, a, bq, bk);
   refine_search(qf, a, bq, bk, qc, ch);
 }
 
@@ -231,11 +232,11 @@ __device__ inline void table_choice(const SweepArgs& a, float bq, int bk, float 
   ch.cs = a.tab_cos[bk];
 }
 
-template <bool kWave = false, class QF>
+template <bool kWave = false, int kUnroll = 8, class QF>
 __device__ inline void table_search(const QF& qf, const SweepArgs& a, float qc, Choice& ch) {
   float bq;
   int bk;
-  scan_table<kWave>(qf, a, bq, bk);
+  scan_table<kWave, kUnroll>(qf, a, bq, bk);
   table_choice(a, bq, bk, qc, ch);
 }
 
@@ -343,10 +344,10 @@ __device__ inline void block_add_count(int v, unsigned long long* acc) {
 
 
 // Seeded search with the fallback done in place.
-template <class QF>
+template <int kUnroll, class QF>
 __device__ inline int seeded_search(const QF& qf, const SweepArgs& a, float seed, float qc, float vin, Choice& ch) {
   if (seeded_local(qf, a, seed, qc, vin, ch)) {
-    full_search(qf, a, qc, ch);
+    full_search<false, kUnroll>(qf, a, qc, ch);
     return 1;
   }
   return 0;
@@ -429,12 +430,6 @@ struct Regions {
   float bnd;  // region 1 <=> displacement offset >= bnd (node offsets)
   bool ok0, ok1;
 };
-
-// Smallest float above x (x finite; 0 maps to the smallest normal float).
-__device__ inline float next_up(float x) {
-  if (x == 0.0f) return 1.17549435e-38f;
-  return __int_as_float(__float_as_int(x) + (x > 0.0f ? 1 : -1));
-}
 
 __device__ inline Regions axis_regions(int i, int n, float d, float g) {
   Regions R;
