@@ -219,11 +219,12 @@ __device__ inline float next_up(float x) {
 // problem a step moves a foot by less than a tenth of a cell), so a search
 // finds the cell and loads the corners only when a foot leaves it.  f: the
 // cell's base minus the node, per axis (NaN: no cell yet, and every foot is
-// looked up); wrap: what the periodic axis subtracts; top1, top2: the largest
-// cell coordinate along v_r and v_t that is still in the cell (1 in the last
-// cell, whose upper face is part of it).
+// looked up); wrap: what the periodic axis subtracts; top: the first offset
+// along r, v_r and v_t above the cell (the last cell's upper face is part of
+// it).  Offsets and not cell coordinates are compared there: one just below a
+// face, which is where a step without motion may round to, has coordinate 1.
 struct CornerCache {
-  float f[4], wrap, top1, top2;
+  float f[4], wrap, top[3];
   CornerPair v[8];
 };
 
@@ -241,8 +242,8 @@ __device__ inline float cached_value(const CornerCache& cc, const float t[4]) {
 }
 
 // I[V] at the foot i + off through the cache.  A foot inside the cached cell
-// takes the coordinates foot_cell would form by the same subtractions (0 <= t
-// < 1 on an axis means that floor(off) is the cached one); any other is looked
+// takes the coordinates foot_cell would form by the same subtractions (f <= off
+// < f + 1 on an axis means that floor(off) is the cached one); any other is looked
 // up by foot_cell, whatever its arrangement.  Along the periodic axis a foot
 // within 2e-5 of the cell's upper face is looked up too (there the wrap's
 // quotient may round up).
@@ -262,7 +263,7 @@ __device__ inline float cached_interp(const float* __restrict__ V, const Grid& G
   if (kCrown) t[3] = (((float)i[3] + off[3]) - cc.wrap) - cc.f[3];
   else t[3] = off[3] - cc.f[3];
   const float low = fminf(fminf(t[0], t[1]), fminf(t[2], t[3]));
-  const bool in = low >= 0.0f && fmaxf(t[0], t[3] + near_top) < 1.0f && o1 < cc.top1 && o2 < cc.top2;
+  const bool in = low >= 0.0f && t[3] + near_top < 1.0f && off[0] < cc.top[0] && o1 < cc.top[1] && o2 < cc.top[2];
   if (!in) {
     // leaving the domain along r: the same answer for every control of most such nodes
     if (!(off[0] >= (float)(-i[0]) && off[0] <= (float)(G.n[0] - 1 - i[0]))) return M;
@@ -279,8 +280,8 @@ __device__ inline float cached_interp(const float* __restrict__ V, const Grid& G
     cc.f[0] = (float)(base[0] - i[0]);
     cc.f[1] = (float)(base[1] - i[1]);
     cc.f[2] = (float)(base[2] - i[2]);
-    cc.top1 = base[1] == G.n[1] - 2 ? next_up(cc.f[1] + 1.0f) : cc.f[1] + 1.0f;
-    cc.top2 = base[2] == G.n[2] - 2 ? next_up(cc.f[2] + 1.0f) : cc.f[2] + 1.0f;
+#pragma unroll
+    for (int k = 0; k < 3; k++) cc.top[k] = base[k] == G.n[k] - 2 ? next_up(cc.f[k] + 1.0f) : cc.f[k] + 1.0f;
     if (kCrown) {
       const float nf = (float)G.n[3];
       cc.wrap = nf * floorf(((float)i[3] + off[3]) / nf);
@@ -290,6 +291,32 @@ __device__ inline float cached_interp(const float* __restrict__ V, const Grid& G
     }
   }
   return cached_value(cc, t);
+}
+
+// The corners alone, with the offset of the cell's lowest corner in V (-1:
+// none): reloaded when the cell changes.
+struct KeyedCorners {
+  int key;
+  CornerCache c;  // only c.v is used
+};
+
+template <bool kCrown>
+__device__ inline float cached_interp(const float* __restrict__ V, const Grid& G, const int i[4], const float off[4],
+                                      float M, KeyedCorners& kc) {
+  int base[4];
+  float t[4];
+  if (!foot_cell(G, i, off, base, t)) return M;
+  const int s3 = (G.periodic3 && base[3] == G.n[3] - 1) ? -base[3] * G.st[3] : G.st[3];
+  const int key = base[0] + base[1] * G.st[1] + base[2] * G.st[2] + base[3] * G.st[3];
+  if (key != kc.key) {
+#pragma unroll
+    for (int e = 0; e < 8; e++) {
+      const int o = ((e & 1) ? G.st[1] : 0) + ((e & 2) ? G.st[2] : 0) + ((e & 4) ? s3 : 0);
+      kc.c.v[e] = *reinterpret_cast<const CornerPair*>(V + key + o);
+    }
+    kc.key = key;
+  }
+  return cached_value(kc.c, t);
 }
 
 // Q1 interpolation of V at s = i + off (paper Section 3: multilinear I[V],
@@ -429,13 +456,15 @@ __device__ inline void cache_init(const NodeTerms& T, const HeunTerms& H, bool h
   }
   for (int k = 0; k < 4; k++) cc.f[k] = NAN;
   cc.wrap = keep ? 0.0f : NAN;
-  cc.top1 = cc.top2 = 0.0f;
+  cc.top[0] = cc.top[1] = cc.top[2] = 0.0f;
 }
 
+__device__ inline void cache_init(const NodeTerms&, const HeunTerms&, bool, KeyedCorners& kc) { kc.key = -1; }
+
 // q_step through a node's cache.
-template <bool kHeun, bool kCrown>
+template <bool kHeun, bool kCrown, class Cache>
 __device__ inline float q_step_cached(const float* __restrict__ V, const Grid& G, const Phys& P, const NodeTerms& T,
-                                      const HeunTerms& H, int thr, float sn, float cs, float qx, CornerCache& cc) {
+                                      const HeunTerms& H, int thr, float sn, float cs, float qx, Cache& cc) {
   float off[4];
   foot_off<kHeun, kCrown>(T, H, thr, sn, cs, off);
   return fmaf(P.gamma, cached_interp<kCrown>(V, G, T.i, off, P.M, cc), (thr ? P.q_thr : P.q_coast) + qx);

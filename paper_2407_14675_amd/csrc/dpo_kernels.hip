@@ -239,12 +239,15 @@ __global__ __launch_bounds__(kBlock) void k_init_value(const uint8_t* __restrict
 // fast path below covers the orbit workloads with the Euler foot.  Bound by
 // vector instruction issue: looking every foot's cell up (four axes with
 // their faces, the periodic one with a division) was half of the instructions.
-// Example 1 (110 x 30 x 30 x 30, 73 controls, Heun foot): 589 -> 389 us, 11,200
+// Example 1 (110 x 30 x 30 x 30, 73 controls, Heun foot): 589 -> 394 us, 11,200
 // -> 6,600 vector instructions per wave; five waves per SIMD at 96 registers (four at 108:
 // 408 us, six with spills: 0.7 ms).  Ordering the nodes as for the factorised
 // sweeps took 414 us: too few nodes here have feet in several cells.
-template <int kMode, bool kHeun, bool kCrown>
-__global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(5))) void k_sweep_direct(SweepArgs a) {
+// kKeyed: only the corners are kept (KeyedCorners), and every evaluation looks its
+// cell up; the form for the Heun foot on grids too small to hide a look-up
+// behind other waves (kKeyedNodes).
+template <int kMode, bool kHeun, bool kCrown, bool kKeyed>
+__global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(kKeyed ? 4 : 5))) void k_sweep_direct(SweepArgs a) {
   const int tile = xcd_tile(blockIdx.x, gridDim.x);
   const int t = tile * kBlock + threadIdx.x;
   double rel = 0, sum = 0, mabs = 0, bad = 0;
@@ -256,14 +259,14 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(5))) voi
     if (kHeun) node_heun(a, T.i, H);
     const float* __restrict__ V = a.V_in;
     const float qx = a.qnode ? a.qnode[j] : 0.0f;
-    CornerCache cc;
+    typename std::conditional<kKeyed, KeyedCorners, CornerCache>::type cc;
     cache_init(T, H, kHeun, cc);
     auto qf = [&](float sn, float cs) { return q_step_cached<kHeun, kCrown>(V, a.G, a.P, T, H, 1, sn, cs, qx, cc); };
     const float qc = q_step_cached<kHeun, kCrown>(V, a.G, a.P, T, H, 0, 0.0f, 1.0f, qx, cc);
     const float vin = V[j];
     Choice ch;
-    // two evaluations in flight: eight copies of the look-up outgrow the instruction cache
-    constexpr int kUnroll = 2;
+    // two evaluations in flight: eight copies of both ways outgrow the instruction cache
+    constexpr int kUnroll = kKeyed ? 8 : 2;
     if (kMode == 0) table_search<false, kUnroll>(qf, a, qc, ch);
     else if (kMode == 1) full_search<false, kUnroll>(qf, a, qc, ch);
     else if (kMode == 3) evals = walk_search(qf, a, a.walk_from[j], qc, ch);
@@ -1017,19 +1020,29 @@ hipError_t launch_init_value(const uint8_t* kind, float M, float* V, int N, hipS
 }
 
 namespace {
-template <bool kHeun, bool kCrown>
+template <bool kHeun, bool kCrown, bool kKeyed>
 hipError_t sweep_direct(const SweepArgs& a, int mode, hipStream_t s) {
   const int nb = blocks_for(a.n_free);
-  if (mode == 0) DPO_LAUNCH((k_sweep_direct<0, kHeun, kCrown>), nb, kBlock, s, a);
-  if (mode == 1) DPO_LAUNCH((k_sweep_direct<1, kHeun, kCrown>), nb, kBlock, s, a);
-  if (mode == 2) DPO_LAUNCH((k_sweep_direct<2, kHeun, kCrown>), nb, kBlock, s, a);
-  DPO_LAUNCH((k_sweep_direct<3, kHeun, kCrown>), nb, kBlock, s, a);
+  if (mode == 0) DPO_LAUNCH((k_sweep_direct<0, kHeun, kCrown, kKeyed>), nb, kBlock, s, a);
+  if (mode == 1) DPO_LAUNCH((k_sweep_direct<1, kHeun, kCrown, kKeyed>), nb, kBlock, s, a);
+  if (mode == 2) DPO_LAUNCH((k_sweep_direct<2, kHeun, kCrown, kKeyed>), nb, kBlock, s, a);
+  DPO_LAUNCH((k_sweep_direct<3, kHeun, kCrown, kKeyed>), nb, kBlock, s, a);
 }
 }  // namespace
 
+// Below one load of the chip at the cell cache's five waves per SIMD a Heun
+// sweep's waves wait for each look-up (scratch and gathers) with nothing beside
+// them.  Heun foot, 72 angles, cell cache / keyed corners: 25 x 15^3 60 / 51 us,
+// 40 x 20^3 94 / 83, 60 x 25^3 179 / 197, 110 x 30^3 394 / 540; the Euler foot is
+// the faster with the cell cache at every size (25 x 15^3: 30 / 38).
+constexpr int kKeyedNodes = 5 * 64 * 1024;
+
 hipError_t launch_sweep_direct(const SweepArgs& a, int mode, hipStream_t s) {
-  if (a.P.model == 2) return a.P.heun ? sweep_direct<true, true>(a, mode, s) : sweep_direct<false, true>(a, mode, s);
-  return a.P.heun ? sweep_direct<true, false>(a, mode, s) : sweep_direct<false, false>(a, mode, s);
+  if (a.P.heun && a.n_free < kKeyedNodes)
+    return a.P.model == 2 ? sweep_direct<true, true, true>(a, mode, s) : sweep_direct<true, false, true>(a, mode, s);
+  if (a.P.model == 2)
+    return a.P.heun ? sweep_direct<true, true, false>(a, mode, s) : sweep_direct<false, true, false>(a, mode, s);
+  return a.P.heun ? sweep_direct<true, false, false>(a, mode, s) : sweep_direct<false, false, false>(a, mode, s);
 }
 
 hipError_t launch_node_cost(const Grid& G, const Phys& P, float* qnode, int N, hipStream_t s) {
