@@ -219,8 +219,7 @@ def greedy_vs_seeded(ctx, V, ang, reps=5):
     12) against the seeded local search (8 thrust evaluations around each
     node's previous angle, the paper's warm start) with its fallback to the
     full search where the result moves the node's value by more than 1e-5
-    relative.  Device time per sweep (events; the seeded sweep includes its
-    second pass over the deferred nodes) and the fraction that fell back."""
+    relative.  Device time per sweep (events) and the fraction that fell back."""
     import torch
 
     from paper_2407_14675_amd import inputs
@@ -251,7 +250,7 @@ def greedy_vs_seeded(ctx, V, ang, reps=5):
     return {"full_search_ms": full_ms, "seeded_ms": seeded_ms, "seeded_over_full": seeded_ms / full_ms,
             "fallback_fraction": fallback, "resid_max_rel": resid,
             "what": "one greedy sweep of the 96^3 x 64 grid on the value the timed steps leave; seeds = the "
-                    "previous greedy angles; kernels k_sweep_fast<1> and k_sweep_fast<2> + k_sweep_fallback"}
+                    "previous greedy angles; kernels k_sweep_fast<1> and k_sweep_fast<2>"}
 
 
 MLP_FLOPS_PER_SAMPLE = 6 * (4 * 128 + 128 * 128 + 128 * 3)  # forward 2 x MAC, backward 4 x MAC

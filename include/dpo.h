@@ -237,8 +237,7 @@ int dpo_bellman_sweep(dpo_ctx* ctx, const float* V_in, float* V_out, float* pol_
 
 /* SEEDED sweep: seed_angle is a device float[N] of proposed thrust angles.
  * Nodes failing the fallback test repeat the SCAN_GOLDEN search; their count
- * is resid[4].  On the factorised path the full searches of sparse fallback
- * nodes run in a second launch over lists the first leaves in node order. */
+ * is resid[4]. */
 int dpo_bellman_sweep_seeded(dpo_ctx* ctx, const float* V_in, float* V_out, float* pol_angle,
                              uint8_t* pol_thr, const float* seed_angle, double* resid,
                              void* stream);

@@ -60,8 +60,6 @@ struct dpo_ctx {
   float* work = nullptr;    // second value buffer of the solvers
   float* work2 = nullptr;   // third value buffer (policy iteration keeps the greedy output while evaluating ahead)
   double* resid_host = nullptr;  // pinned copy of the residual for the overlapped read-back
-  int* fb_list = nullptr;         // seeded sweeps: nodes whose full search is deferred to a second pass
-  int* fb_count = nullptr;
   hipEvent_t resid_ready = nullptr;
   hipEvent_t step_ev[2][4] = {};  // policy iteration: greedy start/end, evaluation start/end, two steps deep
   int* desc_code = nullptr;  // foot descriptors of the greedy step's controls (policy iteration)
@@ -636,23 +634,8 @@ int sweep_seeded(dpo_ctx* c, const float* Vin, float* Vout, float* ang, uint8_t*
     if (e != hipSuccess) return hip_fail(c, e, "seeded sweep launch");
     return DPO_OK;
   }
-  // factorised path: the local searches first, then the full search at the
-  // nodes that fall back, as a second launch over the list the first built
-  const size_t segs = (size_t)blocks_for(c->n_free, 64);
-  if ((!c->fb_list && hipMalloc(&c->fb_list, sizeof(int) * kDeferLanes * segs) != hipSuccess) ||
-      (!c->fb_count && hipMalloc(&c->fb_count, sizeof(int) * segs) != hipSuccess))
-    return fail(c, DPO_ENOMEM, "fallback list alloc");
-  a.fb_list = c->fb_list;
-  a.fb_count = c->fb_count;
-  const int nb1 = blocks_for(c->n_free, c->block);
-  const int nb2 = fallback_blocks(c->n_free, c->block);
   hipError_t e = launch_sweep_fast(a, 2, c->block, s);
-  if (e == hipSuccess) {
-    SweepArgs b = a;
-    b.partial = c->partial + (size_t)kPartial * nb1;
-    e = launch_sweep_fallback(b, c->block, s);
-  }
-  c->last_blocks = nb1 + nb2;
+  c->last_blocks = blocks_for(c->n_free, c->block);
   if (e != hipSuccess) return hip_fail(c, e, "seeded sweep launch");
   return DPO_OK;
 }
@@ -997,7 +980,8 @@ int dpo_create(const dpo_grid* grid, const dpo_problem* prob, const dpo_search* 
       return cleanup(DPO_EHIP);
     }
   }
-  c->partial_blocks = blocks_for(total > 0 ? total : 1, 64) + fallback_blocks(total > 0 ? total : 1, 64);
+  // the brick sweep covers the whole grid, however few of its nodes are free
+  c->partial_blocks = std::max(blocks_for(total > 0 ? total : 1, 64), c->brick_ok ? brick_blocks(c) : 0);
   // the partials, then the first stage of their reduction
   if (hipMalloc(&c->partial, sizeof(double) * kPartial * (c->partial_blocks + kResidStage)) != hipSuccess) {
     c->err = "device allocation failed in dpo_create";
@@ -1044,8 +1028,6 @@ void dpo_destroy(dpo_ctx* c) {
   if (c->resid) hipFree(c->resid);
   if (c->work) hipFree(c->work);
   if (c->work2) hipFree(c->work2);
-  if (c->fb_list) hipFree(c->fb_list);
-  if (c->fb_count) hipFree(c->fb_count);
   if (c->resid_host) hipHostFree(c->resid_host);
   if (c->resid_ready) hipEventDestroy(c->resid_ready);
   for (auto& row : c->step_ev)

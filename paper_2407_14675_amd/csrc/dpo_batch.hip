@@ -39,7 +39,6 @@ __global__ __launch_bounds__(kMaxBlock) __attribute__((amdgpu_waves_per_eu(8))) 
   a.drift3 = nullptr;
   a.seed = a.walk_from = a.pol_ang_in = nullptr;
   a.pol_thr_in = nullptr;
-  a.fb_list = nullptr;
   a.desc_code = nullptr;
   a.desc16 = nullptr;
   a.desc_pk = nullptr;

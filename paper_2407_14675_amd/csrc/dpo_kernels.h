@@ -22,9 +22,6 @@ struct SweepArgs {
   const float* seed;          // seeded search
   const float* walk_from;     // table walk: each node's previous angle (may alias pol_ang)
   unsigned long long* eval_acc;  // table walk: per-workgroup running count of thrust evaluations, nullable
-  int* fb_list;               // seeded search on the factorised path: nodes whose full search is deferred,
-                              // kDeferLanes entries per 64 nodes, nullable
-  int* fb_count;              // their number per 64 nodes
   const uint32_t* free_node;  // packed coordinates (8 bits per axis, r lowest) of the free nodes
   int n_free;
   // factorised sweeps: the free list reordered within chunks of kOrderChunk
@@ -87,11 +84,6 @@ struct SweepArgs {
   int mode;         // search mode (feedback)
   double w_time, w_fuel, lambda;
 };
-
-// At most this many fallback lanes of a wave are deferred to the second pass,
-// whose waves take the lists of kFallbackSegs waves each.
-constexpr int kDeferLanes = 16;
-constexpr int kFallbackSegs = 32;
 
 constexpr int kOrderChunk = 4096;  // entries of the free list ordered together (a multiple of 64)
 
@@ -163,9 +155,6 @@ hipError_t launch_sum_counts(const unsigned long long* acc, int n, unsigned long
 hipError_t launch_policy_eval_desc(const SweepArgs& a, bool streamed, hipStream_t s);
 // format 1: compact codes by free-list position; 2: compact codes by node
 hipError_t launch_policy_eval_desc16(const SweepArgs& a, int format, bool streamed, hipStream_t s);
-// Second pass of a seeded sweep; fallback_blocks: its workgroups for n nodes.
-int fallback_blocks(long long n, int block);
-hipError_t launch_sweep_fallback(const SweepArgs& a, int block, hipStream_t s);
 hipError_t launch_sweep_fast(const SweepArgs& a, int mode, int block, hipStream_t s);
 // Final FP64 reduction of nblocks residual partials into out[kPartial];
 // `stage` holds kResidStage * kPartial doubles for the first of two stages.

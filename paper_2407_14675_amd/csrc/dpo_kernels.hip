@@ -298,40 +298,6 @@ __global__ __launch_bounds__(kMaxBlock) __attribute__((amdgpu_waves_per_eu(8))) 
     block_residual(S.rel, S.sum, S.mabs, S.bad, (double)(kMode == 3 ? S.evals : S.fell_back), a.partial, blockIdx.x);
 }
 
-// Second pass of the seeded sweep: the full search at the nodes the first
-// pass listed, so that a wave's full searches run together instead of
-// stalling the lanes whose local search sufficed.  A wave packs the lists of
-// kFallbackSegs waves of the first pass into full waves of its own (entry e
-// of their sequence by a search in the running counts).  The residual partials
-// of this pass follow those of the first.
-__global__ __launch_bounds__(kMaxBlock) __attribute__((amdgpu_waves_per_eu(8))) void k_sweep_fallback(SweepArgs a) {
-  extern __shared__ float4 dyn_lds[];
-  __shared__ int before[kMaxBlock / 64][kFallbackSegs + 1];
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  const int segs = (a.n_free + 63) >> 6;
-  const int first = (blockIdx.x * (int)(blockDim.x >> 6) + wave) * kFallbackSegs;
-  int sum = lane < kFallbackSegs && first + lane < segs ? a.fb_count[first + lane] : 0;
-#pragma unroll
-  for (int o = 1; o < kFallbackSegs; o <<= 1) {
-    const int up = __shfl_up(sum, o, 64);
-    if (lane >= o) sum += up;
-  }
-  if (lane < kFallbackSegs) before[wave][lane + 1] = sum;
-  if (lane == 0) before[wave][0] = 0;
-  const int total = __shfl(sum, kFallbackSegs - 1, 64);
-  __syncthreads();
-  NodeSums S;
-  for (int e = lane; e < total; e += 64) {
-    int q = 0;
-#pragma unroll
-    for (int h = kFallbackSegs / 2; h > 0; h >>= 1)
-      if (before[wave][q + h] <= e) q += h;
-    const int t = a.fb_list[(first + q) * kDeferLanes + e - before[wave][q]];
-    fast_node<1, false>(a, t, a.sweep_node[t], dyn_lds, nullptr, true, S);
-  }
-  block_residual(S.rel, S.sum, S.mabs, S.bad, 0.0, a.partial, blockIdx.x);
-}
-
 // Frozen-policy sweep (eq:p_eval applied once).  The residual reduction is
 // only compiled in when a caller asks for it; the policy-iteration loop does
 // not, since it stops on the residual of the greedy step.
@@ -1060,14 +1026,6 @@ hipError_t launch_sweep_fast(const SweepArgs& a, int mode, int block, hipStream_
   else if (mode == 1) hipLaunchKernelGGL(k_sweep_fast<1>, dim3(nb), dim3(block), lds, s, a);
   else if (mode == 2) hipLaunchKernelGGL(k_sweep_fast<2>, dim3(nb), dim3(block), lds, s, a);
   else hipLaunchKernelGGL(k_sweep_fast<3>, dim3(nb), dim3(block), lds, s, a);
-  return hipGetLastError();
-}
-
-int fallback_blocks(long long n, int block) { return blocks_for(n, block * kFallbackSegs); }
-
-hipError_t launch_sweep_fallback(const SweepArgs& a, int block, hipStream_t s) {
-  const size_t lds = sizeof(float4) * 4 * (size_t)block;
-  hipLaunchKernelGGL(k_sweep_fallback, dim3(fallback_blocks(a.n_free, block)), dim3(block), lds, s, a);
   return hipGetLastError();
 }
 

@@ -794,12 +794,11 @@ __device__ inline P* in_global(P* p) {
   return (P*)(__attribute__((address_space(1))) P*)p;
 }
 
-// Search of one node with its set-up done: the choice in ch; false where a
-// seeded node's full search is deferred to the second pass.  kMode: 0
+// Search of one node with its set-up done: the choice in ch.  kMode: 0
 // tabulated, 1 scan + golden, 2 seeded, 3 table walk.  scan(bq, bk): the
 // table's first minimum.
 template <int kMode, class QF, class Scan>
-__device__ inline bool search_node(const QF& qf, const Scan& scan, const SweepArgs& a, int j, float qc, float vin,
+__device__ inline void search_node(const QF& qf, const Scan& scan, const SweepArgs& a, int j, float qc, float vin,
                                    Choice& ch, NodeSums& S) {
   float bq;
   int bk;
@@ -812,30 +811,17 @@ __device__ inline bool search_node(const QF& qf, const Scan& scan, const SweepAr
   } else if (kMode == 3) {
     S.evals += walk_search(qf, a, a.walk_from[j], qc, ch);
   } else {
-    const bool need = seeded_local(qf, a, a.seed[j], qc, vin, ch);
-    // A wave where only a few lanes fall back would leave the others idle
-    // through a full search: those lanes are listed for a second pass.
-    // Where many lanes fall back, the wave does the full search in place.
-    const bool few = __popcll(__ballot(need)) <= kDeferLanes;
-    if (need) {
+    // The full search of a lane that falls back holds up its wave.  Listing
+    // such nodes for a second launch was dearer at every size and rate of
+    // fallbacks: the set-up is formed twice, there in mixed waves, while here it
+    // stands in registers and a one-cell wave's scan is short (64 x 60 x 56 x
+    // 48: 324 us with the second launch, 262 in place; 10 x 27 x 12 x 10: 42 and 20).
+    if (seeded_local(qf, a, a.seed[j], qc, vin, ch)) {
       S.fell_back++;
-      if (a.fb_list && few) return false;
       scan(bq, bk);
       refine_search(qf, a, bq, bk, qc, ch);
     }
   }
-  return true;
-}
-
-// Lists the wave's deferred nodes for the second pass, in node order: each
-// wave of 64 nodes has its own kDeferLanes entries and its own count, so no two
-// waves meet (one atomic per wave on a shared count took as long as the sweep
-// itself: 64 x 60 x 56 x 48 nodes, 161,000 waves, 0.48 ms).
-__device__ inline void defer_nodes(const SweepArgs& a, bool deferred, int t) {
-  const unsigned long long bal = __ballot(deferred), here = __ballot(true);
-  const int lane = threadIdx.x & 63, seg = t >> 6;
-  if (lane == __ffsll((long long)here) - 1) a.fb_count[seg] = __popcll(bal);
-  if (deferred) a.fb_list[seg * kDeferLanes + __popcll(bal & ((1ull << lane) - 1ull))] = t;
 }
 
 // Outputs of a node whose choice is made, and its residual contribution.
@@ -870,9 +856,7 @@ __device__ inline void fast_node(const SweepArgs& a, int t, uint32_t packed, flo
     else scan_table(qf, a, bq, bk);
   };
   Choice ch;
-  const bool done = search_node<kMode>(qf, scan, a, j, qc, vin, ch, S);
-  if (kMode == 2 && a.fb_list) defer_nodes(a, !done, t);
-  if (!done) return;
+  search_node<kMode>(qf, scan, a, j, qc, vin, ch, S);
   keep_incumbent(qf, a, j, qc, ch);
   if (a.desc_code || a.desc16 || a.desc_pk) {
     // formats by free-list position: the node's place in node order
