@@ -246,8 +246,11 @@ __device__ inline float cached_value(const CornerCache& cc, const float t[4]) {
 // < f + 1 on an axis means that floor(off) is the cached one); any other is looked
 // up by foot_cell, whatever its arrangement.  Along the periodic axis a foot
 // within 2e-5 of the cell's upper face is looked up too (there the wrap's
-// quotient may round up).
-template <bool kCrown>
+// quotient may round up).  So is a foot that is not a number along v_r or v_t (a
+// proposed or kept angle that is not finite): the clamp to the faces would make
+// it the lower face, and only the look-up, which clamps numbers alone, answers M.
+// (The Heun foot of such an angle is not a number along r either.)
+template <bool kHeun, bool kCrown>
 __device__ inline float cached_interp(const float* __restrict__ V, const Grid& G, const int i[4], const float off[4],
                                       float M, CornerCache& cc) {
   float o1 = off[1], o2 = off[2];
@@ -263,7 +266,8 @@ __device__ inline float cached_interp(const float* __restrict__ V, const Grid& G
   if (kCrown) t[3] = (((float)i[3] + off[3]) - cc.wrap) - cc.f[3];
   else t[3] = off[3] - cc.f[3];
   const float low = fminf(fminf(t[0], t[1]), fminf(t[2], t[3]));
-  const bool in = low >= 0.0f && t[3] + near_top < 1.0f && off[0] < cc.top[0] && o1 < cc.top[1] && o2 < cc.top[2];
+  const bool in = low >= 0.0f && t[3] + near_top < 1.0f && off[0] < cc.top[0] && o1 < cc.top[1] && o2 < cc.top[2] &&
+                  !(kCrown && !kHeun && __builtin_isunordered(off[1], off[2]));
   if (!in) {
     // leaving the domain along r: the same answer for every control of most such nodes
     if (!(off[0] >= (float)(-i[0]) && off[0] <= (float)(G.n[0] - 1 - i[0]))) return M;
@@ -300,7 +304,7 @@ struct KeyedCorners {
   CornerCache c;  // only c.v is used
 };
 
-template <bool kCrown>
+template <bool kHeun, bool kCrown>
 __device__ inline float cached_interp(const float* __restrict__ V, const Grid& G, const int i[4], const float off[4],
                                       float M, KeyedCorners& kc) {
   int base[4];
@@ -439,9 +443,8 @@ __device__ inline float q_step(const float* __restrict__ V, const Grid& G, const
   return fmaf(P.gamma, interp_off<kSnap>(V, G, T.i, off, P.M), (thr ? P.q_thr : P.q_coast) + qx);
 }
 
-// An empty cache.  keep: cells may be kept (every displacement of the node is
-// finite and moderate, so the fast test cannot be fooled by a NaN that the
-// face clamp would hide).
+// An empty cache.  keep: cells may be kept (every term of the node's
+// displacements is finite and moderate, and so is every foot of a finite angle).
 __device__ inline void cache_init(const NodeTerms& T, const HeunTerms& H, bool heun, CornerCache& cc) {
   const float big = 1e6f;
   bool keep = true;
@@ -467,7 +470,7 @@ __device__ inline float q_step_cached(const float* __restrict__ V, const Grid& G
                                       const HeunTerms& H, int thr, float sn, float cs, float qx, Cache& cc) {
   float off[4];
   foot_off<kHeun, kCrown>(T, H, thr, sn, cs, off);
-  return fmaf(P.gamma, cached_interp<kCrown>(V, G, T.i, off, P.M, cc), (thr ? P.q_thr : P.q_coast) + qx);
+  return fmaf(P.gamma, cached_interp<kHeun, kCrown>(V, G, T.i, off, P.M, cc), (thr ? P.q_thr : P.q_coast) + qx);
 }
 
 // The crown problem's orbital-element running cost at a physical state x =
