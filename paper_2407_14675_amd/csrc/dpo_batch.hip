@@ -20,21 +20,22 @@ __global__ __launch_bounds__(kMaxBlock) __attribute__((amdgpu_waves_per_eu(8))) 
   const int k = __builtin_amdgcn_readfirstlane(B.tile_run[tile]);
   const ConstArgs p = (ConstArgs)(B.sweeps + parity * B.n_run + k);
   SweepArgs a = *(const SweepArgs*)p;
-  a.V_in = in_global(a.V_in);
-  a.V_out = in_global(a.V_out);
-  a.pol_ang = in_global(a.pol_ang);
-  a.pol_thr = in_global(a.pol_thr);
-  a.sweep_node = in_global(a.sweep_node);
-  a.one_cell = in_global(a.one_cell);
-  a.rinv = in_global(a.rinv);
-  a.drift0 = in_global(a.drift0);
-  a.drift1 = in_global(a.drift1);
-  a.drift2 = in_global(a.drift2);
-  a.mrow = in_global(a.mrow);
-  a.tab_sin = in_global(a.tab_sin);
-  a.tab_cos = in_global(a.tab_cos);
-  a.tab_ang = in_global(a.tab_ang);
-  a.rot_scan = in_global(a.rot_scan);
+  // pointers one by one through the constant address space (see ConstArgs)
+  a.V_in = p->V_in;
+  a.V_out = p->V_out;
+  a.pol_ang = p->pol_ang;
+  a.pol_thr = p->pol_thr;
+  a.sweep_node = p->sweep_node;
+  a.one_cell = p->one_cell;
+  a.rinv = p->rinv;
+  a.drift0 = p->drift0;
+  a.drift1 = p->drift1;
+  a.drift2 = p->drift2;
+  a.mrow = p->mrow;
+  a.tab_sin = p->tab_sin;
+  a.tab_cos = p->tab_cos;
+  a.tab_ang = p->tab_ang;
+  a.rot_scan = p->rot_scan;
   // what a batched sweep does not have
   a.drift3 = nullptr;
   a.seed = a.walk_from = a.pol_ang_in = nullptr;

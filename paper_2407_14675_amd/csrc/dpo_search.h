@@ -786,13 +786,11 @@ struct NodeSums {
 };
 
 // Arguments read from memory instead of the kernel's argument block (the
-// batched sweep): by scalar loads, the pointers marked as global memory (the
-// compiler would otherwise have to use flat loads and stores for them).
+// batched sweep): by scalar loads.  A pointer loaded through this type is
+// known to be global memory; one that is copied with the whole struct, or cast
+// to global memory and back, is not, and its accesses become flat instructions,
+// which take no scalar base and wait on both counters.
 typedef const __attribute__((address_space(4))) SweepArgs* ConstArgs;
-template <class P>
-__device__ inline P* in_global(P* p) {
-  return (P*)(__attribute__((address_space(1))) P*)p;
-}
 
 // Search of one node with its set-up done: the choice in ch.  kMode: 0
 // tabulated, 1 scan + golden, 2 seeded, 3 table walk.  scan(bq, bk): the

@@ -1,0 +1,34 @@
+"""What the compiler made of the sweep kernels, on the CPU: their gfx950
+assembly, built from the sources with the library's own flags."""
+import os
+import re
+import subprocess
+
+import pytest
+
+from paper_2407_14675_amd import build
+
+
+@pytest.fixture(scope="module")
+def kernels(tmp_path_factory):
+    """source -> {kernel symbol: assembly}."""
+    def compiled(source):
+        out = tmp_path_factory.mktemp("asm") / (source + ".s")
+        subprocess.run([build.HIPCC, *build.FLAGS, "-S", "--cuda-device-only", os.path.join(build.CSRC, source), "-o",
+                        str(out)], check=True, stderr=subprocess.DEVNULL)
+        text = out.read_text()
+        found = {m[1]: m[0] for m in re.finditer(r"\n(_Z\w+):[^\n]*\n.*?\n\.Lfunc_end", text, re.S)}
+        assert found
+        return found
+
+    return {s: compiled(s) for s in ("dpo_batch.hip", "dpo_kernels.hip")}
+
+
+@pytest.mark.parametrize("source,name,count", [("dpo_batch.hip", "k_batch_sweep", 2), ("dpo_kernels.hip", "k_sweep_fast", 4)])
+def test_sweeps_address_global_memory(kernels, source, name, count):
+    """No flat access, which cannot take a scalar base and waits on the LDS counter too."""
+    found = {k: v for k, v in kernels[source].items() if name in k}
+    assert len(found) == count
+    for k, text in found.items():
+        assert len(re.findall(r"\tglobal_load", text)) > 10, k
+        assert not re.findall(r"\tflat_\w+", text), k
