@@ -1709,8 +1709,9 @@ dpo::CtxView dpo::ctx_view(const dpo_ctx* c) {
 }
 
 // ============================================================ batched solve
-// The batch keeps the problems' values (A and B) and policies in one
-// concatenated device allocation each, the rest in the problems' own contexts.
+// The batch keeps the problems' values (A and B) in one concatenated device
+// allocation each, the rest in the problems' own contexts; the policy is
+// written where the caller wants it, whose fixed nodes stay as they are.
 struct dpo_batch {
   int n = 0;
   std::vector<dpo_ctx*> ctx;
@@ -1720,8 +1721,6 @@ struct dpo_batch {
   std::vector<long long> v_off;  // node offsets (n + 1)
   float* Va = nullptr;
   float* Vb = nullptr;
-  float* ang = nullptr;
-  uint8_t* thr = nullptr;
   SweepArgs* d_sweeps = nullptr;  // sweep arguments of the running problems, in run order: A -> B, then B -> A (2 n)
   int* d_tile_begin = nullptr;  // over the running problems (n + 1)
   int* d_tile_run = nullptr;    // running problem of each tile (partial_cap)
@@ -1748,10 +1747,16 @@ int bfail(dpo_batch* b, int code, const std::string& msg) {
     if (e_ != hipSuccess) return bfail((b), DPO_EHIP, std::string(#call) + ": " + hipGetErrorString(e_)); \
   } while (0)
 
+// Where a batched solve writes its policies, per problem (null: nowhere).
+struct BatchPolicy {
+  float* const* ang;
+  uint8_t* const* thr;
+};
+
 // Tile table over the running problems for workgroups of `block` threads, and
 // their sweep arguments for both directions of the value buffers (uploaded);
 // returns the tile count.
-int batch_tables(dpo_batch* b, int block, const std::vector<int>& run, bool policy, int* n_tiles) {
+int batch_tables(dpo_batch* b, int block, const std::vector<int>& run, const BatchPolicy& policy, int* n_tiles) {
   const size_t n = run.size();
   std::vector<int> tb(n + 1, 0);
   std::vector<SweepArgs> rec(2 * n);
@@ -1759,8 +1764,8 @@ int batch_tables(dpo_batch* b, int block, const std::vector<int>& run, bool poli
     const dpo_ctx* c = b->ctx[run[k]];
     const long long off = b->v_off[run[k]];
     SweepArgs a = base_args(c);
-    a.pol_ang = policy ? b->ang + off : nullptr;
-    a.pol_thr = policy ? b->thr + off : nullptr;
+    a.pol_ang = policy.ang ? policy.ang[run[k]] : nullptr;
+    a.pol_thr = policy.thr ? policy.thr[run[k]] : nullptr;
     for (int parity = 0; parity < 2; parity++) {
       a.V_in = (parity ? b->Vb : b->Va) + off;
       a.V_out = (parity ? b->Va : b->Vb) + off;
@@ -1819,7 +1824,7 @@ int batch_graph(dpo_batch* b, const BatchArgs& a, int block, int S, hipGraphExec
 
 // Replays until every problem has stopped or max_sweeps; the graph is
 // re-captured over the remaining problems whenever one stops.
-int batch_run(dpo_batch* b, double tol, int64_t max_sweeps, int S, int block, bool policy,
+int batch_run(dpo_batch* b, double tol, int64_t max_sweeps, int S, int block, const BatchPolicy& policy,
               std::vector<int64_t>& sweeps, std::vector<int>& done, int64_t* total) {
   const int n = b->n;
   std::vector<int> run(n);
@@ -1923,7 +1928,6 @@ int dpo_batch_create(int32_t n_prob, const dpo_grid* grids, const dpo_problem* p
   }
   b->partial_cap = (int)std::max(1LL, tiles64);
   if (hipMalloc(&b->Va, sizeof(float) * NT) != hipSuccess || hipMalloc(&b->Vb, sizeof(float) * NT) != hipSuccess ||
-      hipMalloc(&b->ang, sizeof(float) * NT) != hipSuccess || hipMalloc(&b->thr, (size_t)NT) != hipSuccess ||
       hipMalloc(&b->d_sweeps, sizeof(SweepArgs) * 2 * n_prob) != hipSuccess ||
       hipMalloc(&b->d_tile_begin, sizeof(int) * (n_prob + 1)) != hipSuccess ||
       hipMalloc(&b->d_tile_run, sizeof(int) * b->partial_cap) != hipSuccess ||
@@ -1949,8 +1953,7 @@ void dpo_batch_destroy(dpo_batch* b) {
   if (!b) return;
   if (b->stream) hipStreamSynchronize(b->stream);
   for (dpo_ctx* c : b->ctx) dpo_destroy(c);
-  void* bufs[] = {b->Va, b->Vb, b->ang, b->thr, b->d_sweeps,
-                  b->d_tile_begin, b->d_tile_run, b->d_run, b->d_done, b->d_partial, b->d_resid};
+  void* bufs[] = {b->Va, b->Vb, b->d_sweeps, b->d_tile_begin, b->d_tile_run, b->d_run, b->d_done, b->d_partial, b->d_resid};
   for (void* v : bufs)
     if (v) hipFree(v);
   if (b->stream) hipStreamDestroy(b->stream);
@@ -1989,7 +1992,8 @@ int dpo_batch_solve_vi(dpo_batch* b, float* const* V, float* const* pol_angle, u
   int rc = check_batch_cfg(b, block, sweeps_per_graph);
   if (rc != DPO_OK) return rc;
   const int n = b->n;
-  const bool policy = pol_angle && pol_thr;
+  const bool both = pol_angle && pol_thr;
+  const BatchPolicy policy{both ? pol_angle : nullptr, both ? pol_thr : nullptr};
   BHIP_TRY(b, hipStreamSynchronize(reinterpret_cast<hipStream_t>(stream)));
   const double t0 = now_s();
   if ((rc = batch_copy_values(b, V, b->Va, true)) != DPO_OK) return rc;
@@ -2005,10 +2009,6 @@ int dpo_batch_solve_vi(dpo_batch* b, float* const* V, float* const* pol_angle, u
   for (int p = 0; p < n; p++) {
     const size_t N = (size_t)b->ctx[p]->N;
     BHIP_TRY(b, hipMemcpyAsync(V[p], b->Va + b->v_off[p], sizeof(float) * N, hipMemcpyDeviceToDevice, b->stream));
-    if (policy) {
-      BHIP_TRY(b, hipMemcpyAsync(pol_angle[p], b->ang + b->v_off[p], sizeof(float) * N, hipMemcpyDeviceToDevice, b->stream));
-      BHIP_TRY(b, hipMemcpyAsync(pol_thr[p], b->thr + b->v_off[p], N, hipMemcpyDeviceToDevice, b->stream));
-    }
     if (done[p] == 2) code = DPO_ENUMERIC;
     else if (done[p] == 0 && code == DPO_OK) code = DPO_ENOCONV;
     if (stats) {
@@ -2044,7 +2044,7 @@ int dpo_batch_time_config(dpo_batch* b, int32_t block, int32_t sweeps_per_graph,
   std::vector<int> run(n);
   for (int p = 0; p < n; p++) run[p] = p;
   int n_tiles = 0;
-  if ((rc = batch_tables(b, block, run, false, &n_tiles)) != DPO_OK) return rc;
+  if ((rc = batch_tables(b, block, run, BatchPolicy{nullptr, nullptr}, &n_tiles)) != DPO_OK) return rc;
   BHIP_TRY(b, hipMemsetAsync(b->d_done, 0, sizeof(int) * n, b->stream));
   hipGraphExec_t exec = nullptr;
   if ((rc = batch_graph(b, batch_args(b, -1.0, run, n_tiles), block, sweeps_per_graph, &exec)) != DPO_OK) return rc;
