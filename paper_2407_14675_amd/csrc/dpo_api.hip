@@ -1794,7 +1794,6 @@ BatchArgs batch_args(dpo_batch* b, double tol, const std::vector<int>& run, int 
   a.tile_run = b->d_tile_run;
   a.n_run = (int)run.size();
   a.n_tiles = n_tiles;
-  a.n_ang = b->ctx[0]->n_ang;
   a.done = b->d_done;
   a.partial = b->d_partial;
   a.resid = b->d_resid;

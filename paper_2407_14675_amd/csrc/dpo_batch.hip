@@ -84,7 +84,7 @@ __global__ __launch_bounds__(kBlock) void k_batch_reduce(BatchArgs B) {
 }
 
 hipError_t launch_batch_sweep(const BatchArgs& b, int mode, int block, int parity, int want_resid, hipStream_t s) {
-  const size_t lds = sweep_lds_bytes(block, b.n_ang);
+  const size_t lds = sweep_lds_bytes(block);
   if (mode == 0) hipLaunchKernelGGL(k_batch_sweep<0>, dim3(b.n_tiles), dim3(block), lds, s, b, parity, want_resid);
   else hipLaunchKernelGGL(k_batch_sweep<1>, dim3(b.n_tiles), dim3(block), lds, s, b, parity, want_resid);
   return hipGetLastError();

@@ -121,7 +121,6 @@ struct BatchArgs {
   const int* tile_run;        // running problem of each tile (n_tiles entries)
   int n_run;
   int n_tiles;
-  int n_ang;      // shared search table
   int* done;      // per problem: 0 running, 1 converged, 2 non-finite values
   double* partial;
   double* resid;  // kPartial per problem

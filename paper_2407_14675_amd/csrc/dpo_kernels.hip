@@ -1021,7 +1021,7 @@ hipError_t launch_sum_counts(const unsigned long long* acc, int n, unsigned long
 
 hipError_t launch_sweep_fast(const SweepArgs& a, int mode, int block, hipStream_t s) {
   const int nb = blocks_for(a.n_free, block);
-  const size_t lds = sweep_lds_bytes(block, a.n_ang);
+  const size_t lds = sweep_lds_bytes(block);
   if (mode == 0) hipLaunchKernelGGL(k_sweep_fast<0>, dim3(nb), dim3(block), lds, s, a);
   else if (mode == 1) hipLaunchKernelGGL(k_sweep_fast<1>, dim3(nb), dim3(block), lds, s, a);
   else if (mode == 2) hipLaunchKernelGGL(k_sweep_fast<2>, dim3(nb), dim3(block), lds, s, a);

@@ -730,29 +730,67 @@ __device__ inline int scan_window(const SweepArgs& a, const CellNode& F, int& k0
   return n;
 }
 
-// scan_table for a one-cell node: the window where every active lane of the
-// wave has one (lanes in step through their own windows), else the whole
-// table.  tab: (sin, cos) of the table in LDS.
-__device__ inline void scan_cell(const SweepArgs& a, const CellNode& F, const float2* tab, float& bq, int& bk) {
-  auto qf = [&](float sn, float cs) { return cell_q(F, sn, cs); };
-  int k;
-  const int n = scan_window(a, F, k);
-  if (!__all(n > 0)) {
-    scan_table(qf, a, bq, bk);
-    return;
-  }
+// The angle table as a one-cell wave reads it, each lane at its own entry: in
+// LDS, in the region pairs' place, which such a wave leaves unused (four runs
+// of 64 float4, a workgroup's width apart).  Every wave fills its own, so that
+// no other waits for it: a table of the whole workgroup's behind the region pairs
+// held up the general waves too and took LDS in all modes (scan 64 + golden 12,
+// 12^4: 15.8 us a sweep with it, 15.6 now; seeded 9.7 and 9.1).  Tables of more than
+// kWaveAngles entries do not fit and are read from memory (1024 samples, 32^4: 302 us
+// with the workgroup's table, 299 now).
+constexpr int kWaveAngles = 512;
+
+struct WaveAngles {
+  float2* run;  // the wave's first run
+  int stride;   // float2 from one run to the next
+  float2 own;   // the lane's entry of the first 64, on its way from memory
+  __device__ float2& at(int k) const { return run[(k >> 7) * stride + (k & 127)]; }
+};
+
+__device__ inline void load_angles(const SweepArgs& a, float4* lds, WaveAngles& W) {
+  const int k = min((int)(threadIdx.x & 63), a.n_ang - 1);
+  W.run = reinterpret_cast<float2*>(lds + ((int)threadIdx.x & ~63));
+  W.stride = 2 * (int)blockDim.x;
+  W.own = make_float2(a.tab_sin[k], a.tab_cos[k]);
+}
+
+// All lanes of the wave call it.
+__device__ inline void store_angles(const SweepArgs& a, const WaveAngles& W) {
+  if (a.n_ang > kWaveAngles) return;
+  int k = threadIdx.x & 63;
+  W.at(k) = W.own;  // entries past the table's end are not read
+  for (k += 64; k < a.n_ang; k += 64) W.at(k) = make_float2(a.tab_sin[k], a.tab_cos[k]);
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
+// The first minimum of the n table entries from k on, in table order also
+// where they wrap around the table's end; at(k): an entry's sin and cos.
+template <class At>
+__device__ inline void scan_entries(const SweepArgs& a, const CellNode& F, const At& at, int k, int n, float& bq, int& bk) {
   bq = INFINITY;
   bk = 0;
   for (int i = 0; i < n; i++) {
-    const float2 sc = tab[k];
-    const float q = qf(sc.x, sc.y);
-    // the first minimum in table order, also where the window wraps around the table's end
+    const float2 sc = at(k);
+    const float q = cell_q(F, sc.x, sc.y);
     if (q < bq || (q == bq && k < bk)) {
       bq = q;
       bk = k;
     }
     k = k + 1 == a.n_ang ? 0 : k + 1;
   }
+}
+
+// scan_table for a one-cell node: the window where every active lane of the
+// wave has one (lanes in step through their own windows), else the whole
+// table.
+__device__ inline void scan_cell(const SweepArgs& a, const CellNode& F, const WaveAngles& W, float& bq, int& bk) {
+  int k;
+  const int n = scan_window(a, F, k);
+  if (!__all(n > 0)) scan_table([&](float sn, float cs) { return cell_q(F, sn, cs); }, a, bq, bk);
+  else if (a.n_ang <= kWaveAngles) scan_entries(a, F, [&](int e) { return W.at(e); }, k, n, bq, bk);
+  else scan_entries(a, F, [&](int e) { return make_float2(a.tab_sin[e], a.tab_cos[e]); }, k, n, bq, bk);
 }
 
 // write_desc for a one-cell node: the cell of every foot is known, and its
@@ -831,14 +869,16 @@ __device__ inline void store_node(const SweepArgs& a, int j, float vin, const Ch
 }
 
 // One free node of a sweep on the factorised path.  kOne: its thrust feet
-// share one cell.  lds: 4 * blockDim.x float4 (general form); tab: (sin, cos)
-// of the table (one-cell form).
+// share one cell.  lds: 4 * blockDim.x float4 (general form: the region pairs;
+// one-cell form: the wave's angles).
 template <int kMode, bool kOne>
-__device__ inline void fast_node(const SweepArgs& a, int t, uint32_t packed, float4* lds, const float2* tab, bool resid,
-                                 NodeSums& S) {
+__device__ inline void fast_node(const SweepArgs& a, int t, uint32_t packed, float4* lds, bool resid, NodeSums& S) {
   NodeTerms T;
   const int j = node_terms_tab(a, packed, T);
   const float vin = (resid || kMode == 2) ? a.V_in[j] : 0.0f;
+  constexpr bool kAngles = kOne && (kMode == 1 || kMode == 2);
+  WaveAngles W;
+  if constexpr (kAngles) load_angles(a, lds, W);
   FeetCells C;
   feet_cells<kOne>(a, T, C);
   typename std::conditional<kOne, CellNode, FastNode>::type F;
@@ -849,12 +889,17 @@ __device__ inline void fast_node(const SweepArgs& a, int t, uint32_t packed, flo
     if constexpr (kOne) return cell_q(F, sn, cs);
     else return fast_q(F, sn, cs);
   };
+  if constexpr (kAngles) store_angles(a, W);
   auto scan = [&](float& bq, int& bk) {
-    if constexpr (kOne && kMode != 0) scan_cell(a, F, tab, bq, bk);
+    if constexpr (kAngles) scan_cell(a, F, W, bq, bk);
     else scan_table(qf, a, bq, bk);
   };
   Choice ch;
   search_node<kMode>(qf, scan, a, j, qc, vin, ch, S);
+  if (t >= a.n_free) {
+    S = NodeSums();
+    return;
+  }
   keep_incumbent(qf, a, j, qc, ch);
   if (a.desc_code || a.desc16 || a.desc_pk) {
     // formats by free-list position: the node's place in node order
@@ -881,23 +926,17 @@ __device__ inline void sweep_nodes(const SweepArgs& a, int tile, float4* lds, bo
   const int bd = (int)blockDim.x, tid = (int)threadIdx.x;
   const int first = __builtin_amdgcn_readfirstlane(tile * bd + (tid & ~63));
   const int t = first + (tid & 63), in_wave = min(64, a.n_free - first);
-  // the node, the kind of its wave and the table are loaded together: a
-  // sweep of few controls waits on memory, not on arithmetic
-  const uint32_t packed = t < a.n_free ? a.sweep_node[t] : 0u;
-  const bool one = in_wave > 0 && (first & (kOrderChunk - 1)) + in_wave <= a.one_cell[first / kOrderChunk];
-  float2* tab = reinterpret_cast<float2*>(lds + 4 * bd);
-  if (kMode == 1 || kMode == 2) {
-    for (int k = tid; k < a.n_ang; k += bd) tab[k] = make_float2(a.tab_sin[k], a.tab_cos[k]);
-    __syncthreads();
-  }
-  if (t >= a.n_free) return;
-  if (one) fast_node<kMode, true>(a, t, packed, lds, tab, resid, S);
-  else fast_node<kMode, false>(a, t, packed, lds, tab, resid, S);
+  if (in_wave <= 0) return;
+  // the node and the kind of its wave are loaded together: a sweep of few
+  // controls waits on memory, not on arithmetic.  Lanes beyond the list's end
+  // go with its last node and store nothing.
+  const uint32_t packed = a.sweep_node[min(t, a.n_free - 1)];
+  const bool one = (first & (kOrderChunk - 1)) + in_wave <= a.one_cell[first / kOrderChunk];
+  if (one) fast_node<kMode, true>(a, t, packed, lds, resid, S);
+  else fast_node<kMode, false>(a, t, packed, lds, resid, S);
 }
 
 // Dynamic LDS of sweep_nodes.
-inline size_t sweep_lds_bytes(int block, int n_ang) {
-  return sizeof(float4) * 4 * (size_t)block + sizeof(float2) * (size_t)n_ang;
-}
+inline size_t sweep_lds_bytes(int block) { return sizeof(float4) * 4 * (size_t)block; }
 
 }  // namespace dpo

@@ -32,3 +32,10 @@ def test_sweeps_address_global_memory(kernels, source, name, count):
     for k, text in found.items():
         assert len(re.findall(r"\tglobal_load", text)) > 10, k
         assert not re.findall(r"\tflat_\w+", text), k
+
+
+def test_no_wave_waits_for_the_angle_table(kernels):
+    """The scan + golden and seeded sweeps have the residual's barriers and no other."""
+    barriers = [len(re.findall(r"\ts_barrier", kernels["dpo_kernels.hip"][f"_ZN3dpo12k_sweep_fastILi{m}EEEvNS_9SweepArgsE"]))
+                for m in (0, 1, 2)]
+    assert barriers[0] > 0 and barriers[1] == barriers[2] == barriers[0]
