@@ -19,32 +19,8 @@ __global__ __launch_bounds__(kMaxBlock) __attribute__((amdgpu_waves_per_eu(8))) 
   const int tile = xcd_tile(blockIdx.x, gridDim.x);
   const int k = __builtin_amdgcn_readfirstlane(B.tile_run[tile]);
   const ConstArgs p = (ConstArgs)(B.sweeps + parity * B.n_run + k);
-  SweepArgs a = *(const SweepArgs*)p;
-  // pointers one by one through the constant address space (see ConstArgs)
-  a.V_in = p->V_in;
-  a.V_out = p->V_out;
-  a.pol_ang = p->pol_ang;
-  a.pol_thr = p->pol_thr;
-  a.sweep_node = p->sweep_node;
-  a.one_cell = p->one_cell;
-  a.rinv = p->rinv;
-  a.drift0 = p->drift0;
-  a.drift1 = p->drift1;
-  a.drift2 = p->drift2;
-  a.mrow = p->mrow;
-  a.tab_sin = p->tab_sin;
-  a.tab_cos = p->tab_cos;
-  a.tab_ang = p->tab_ang;
-  a.rot_scan = p->rot_scan;
-  // what a batched sweep does not have
-  a.drift3 = nullptr;
-  a.seed = a.walk_from = a.pol_ang_in = nullptr;
-  a.pol_thr_in = nullptr;
-  a.desc_code = nullptr;
-  a.desc16 = nullptr;
-  a.desc_pk = nullptr;
   NodeSums S;
-  sweep_nodes<kMode>(a, tile - B.tile_begin[k], dyn_lds, want_resid != 0, S);
+  sweep_nodes<kMode, true>(p, tile - B.tile_begin[k], dyn_lds, want_resid != 0, S);
   // only the last sweep of a graph replay feeds the stop decision
   if (want_resid) block_residual(S.rel, S.sum, S.mabs, S.bad, (double)S.fell_back, B.partial, tile);
 }

@@ -183,9 +183,10 @@ __global__ __launch_bounds__(kBlock) void k_order_free(SweepArgs a, uint32_t* __
     bool one = false;
     if (e < hi) {
       NodeTerms T;
-      node_terms_tab(a, a.free_node[base + e], T);
+      float4 m;
+      node_terms_tab(a, a.free_node[base + e], T, m);
       FeetCells C;
-      feet_cells<false>(a, T, C);
+      feet_cells<false>(a, T, m, C);
       one = C.one_cell();
     }
     kinds[r] = __ballot(one);
@@ -290,7 +291,7 @@ __global__ __launch_bounds__(kMaxBlock) __attribute__((amdgpu_waves_per_eu(8))) 
   extern __shared__ float4 dyn_lds[];
   const int tile = xcd_tile(blockIdx.x, gridDim.x);
   NodeSums S;
-  sweep_nodes<kMode>(a, tile, dyn_lds, a.partial != nullptr, S);
+  sweep_nodes<kMode, false>((ConstArgs)__builtin_amdgcn_kernarg_segment_ptr(), tile, dyn_lds, a.partial != nullptr, S);
   if (kMode == 3 && a.eval_acc) block_add_count(S.evals, a.eval_acc);
   // a null partial buffer (value-iteration sweeps between checks) skips the residual;
   // the fifth entry: seeded fallbacks, or the walk's thrust evaluations

@@ -53,22 +53,32 @@ __device__ inline void node_terms_calc(const SweepArgs& a, const float* g1tab, c
 // The same from the context's tables: every term depends on one or two of the
 // coordinates only (the drift along v_t is one FP64 product of two of them),
 // so a node reads a few cached entries instead of some twenty FP64 operations.
-__device__ inline void node_terms_at(const SweepArgs& a, NodeTerms& T) {
+// m: the node's mass plane's row, for feet_cells.
+__device__ inline void node_terms_at(const SweepArgs& a, NodeTerms& T, float4& m) {
 #pragma clang fp contract(off)
   T.drift[0] = a.drift0[T.i[1]];
   T.drift[1] = a.drift1[__umul24(T.i[2], a.G.n[0]) + T.i[0]];
   T.drift[2] = (float)(a.drift2[__umul24(T.i[2], a.G.n[1]) + T.i[1]] * a.rinv[T.i[0]]);
   T.drift[3] = a.drift3 ? a.drift3[__umul24(T.i[2], a.G.n[0]) + T.i[0]] : 0.0f;
-  const float4 m = a.mrow[T.i[3]];
+  m = a.mrow[T.i[3]];
   T.g1 = m.x;
   T.g2 = m.y;
   T.gm = a.gm;
 }
 
-__device__ inline int node_terms_tab(const SweepArgs& a, uint32_t packed, NodeTerms& T) {
+__device__ inline void node_terms_at(const SweepArgs& a, NodeTerms& T) {
+  float4 m;
+  node_terms_at(a, T, m);
+}
+
+__device__ inline int node_terms_tab(const SweepArgs& a, uint32_t packed, NodeTerms& T, float4& m) {
   const int j = unpack_node(a.G, packed, T.i);
-  node_terms_at(a, T);
+  node_terms_at(a, T, m);
   return j;
+}
+__device__ inline int node_terms_tab(const SweepArgs& a, uint32_t packed, NodeTerms& T) {
+  float4 m;
+  return node_terms_tab(a, packed, T, m);
 }
 
 // A table that no kernel of the launch writes, read at an index all lanes
@@ -510,13 +520,12 @@ __device__ inline Regions axis_one_region(int i, int n, float d, float g) {
 }
 
 template <bool kOne>
-__device__ inline void feet_cells(const SweepArgs& a, const NodeTerms& T, FeetCells& C) {
+__device__ inline void feet_cells(const SweepArgs& a, const NodeTerms& T, const float4& m, FeetCells& C) {
   const Grid& G = a.G;
   C.br = 0;
   C.tr = 0.0f;
   C.ok_r = axis_cell(T.i[0], G.n[0], T.drift[0], C.br, C.tr);
   // m cell under thrust; the coast foot stays on plane i_m
-  const float4 m = a.mrow[T.i[3]];
   const uint32_t w = __float_as_uint(m.w);
   C.tm = m.z;
   C.plane = w & ~3u;
@@ -823,12 +832,62 @@ struct NodeSums {
   int fell_back = 0, evals = 0;
 };
 
-// Arguments read from memory instead of the kernel's argument block (the
-// batched sweep): by scalar loads.  A pointer loaded through this type is
-// known to be global memory; one that is copied with the whole struct, or cast
-// to global memory and back, is not, and its accesses become flat instructions,
-// which take no scalar base and wait on both counters.
+// The sweep's arguments where they lie in constant memory (the kernel's
+// argument block, or a record of the batched sweep).
 typedef const __attribute__((address_space(4))) SweepArgs* ConstArgs;
+
+// The same address, of which the compiler knows nothing: what is read through
+// it is loaded there and not ahead of it.
+__device__ inline ConstArgs anew(ConstArgs p) {
+  asm volatile("" : "+s"(p));
+  return p;
+}
+
+// Brings the cache lines of the arguments in, all at once: read piece by piece
+// later, each would be a trip to memory of its own.
+__device__ inline void touch_args(ConstArgs p) {
+  static_assert(sizeof(SweepArgs) > 9 * 64 && sizeof(SweepArgs) <= 10 * 64, "one word of every 64 bytes");
+  const auto* w = (const __attribute__((address_space(4))) int*)p;
+  asm volatile("" ::"s"(w[0]), "s"(w[16]), "s"(w[32]), "s"(w[48]), "s"(w[64]), "s"(w[80]), "s"(w[96]), "s"(w[112]),
+               "s"(w[128]), "s"(w[144]));
+}
+
+// The arguments through p, each loaded where it is first used.  The pointers
+// are read one by one through the constant address space: only such a load is
+// known to give global memory (a pointer copied as part of the struct, or cast to global
+// memory and back, is accessed by flat instructions).  kBatch: without what
+// a batched sweep does not have.
+template <bool kBatch>
+__device__ inline SweepArgs sweep_args(ConstArgs p) {
+  SweepArgs a = *(const SweepArgs*)p;
+  a.V_in = p->V_in;
+  a.V_out = p->V_out;
+  a.pol_ang = p->pol_ang;
+  a.pol_thr = p->pol_thr;
+  a.sweep_node = p->sweep_node;
+  a.sweep_pos = p->sweep_pos;
+  a.one_cell = p->one_cell;
+  a.rinv = p->rinv;
+  a.drift0 = p->drift0;
+  a.drift1 = p->drift1;
+  a.drift2 = p->drift2;
+  a.drift3 = nullptr;  // the crown problem takes the direct path
+  a.mrow = p->mrow;
+  a.tab_sin = p->tab_sin;
+  a.tab_cos = p->tab_cos;
+  a.tab_ang = p->tab_ang;
+  a.rot_scan = p->rot_scan;
+  a.rot_local = p->rot_local;
+  a.seed = kBatch ? nullptr : p->seed;
+  a.walk_from = kBatch ? nullptr : p->walk_from;
+  a.pol_ang_in = kBatch ? nullptr : p->pol_ang_in;
+  a.pol_thr_in = kBatch ? nullptr : p->pol_thr_in;
+  a.desc_code = kBatch ? nullptr : p->desc_code;
+  a.desc16 = kBatch ? nullptr : p->desc16;
+  a.desc_pk = kBatch ? nullptr : p->desc_pk;
+  a.desc_w = kBatch ? nullptr : p->desc_w;
+  return a;
+}
 
 // Search of one node with its set-up done: the choice in ch.  kMode: 0
 // tabulated, 1 scan + golden, 2 seeded, 3 table walk.  scan(bq, bk): the
@@ -869,18 +928,25 @@ __device__ inline void store_node(const SweepArgs& a, int j, float vin, const Ch
 }
 
 // One free node of a sweep on the factorised path.  kOne: its thrust feet
-// share one cell.  lds: 4 * blockDim.x float4 (general form: the region pairs;
-// one-cell form: the wave's angles).
-template <int kMode, bool kOne>
-__device__ inline void fast_node(const SweepArgs& a, int t, uint32_t packed, float4* lds, bool resid, NodeSums& S) {
+// share one cell.  live: not a lane beyond the list's end.  lds: 4 * blockDim.x
+// float4 (general form: the region pairs; one-cell form: the wave's angles).
+// The arguments of the set-up, the search and the outputs are loaded each at
+// its place: both forms' together do not fit the scalar registers (23-49 of them
+// were spilled to lanes of vector registers, stored one by one ahead of every node;
+// 12^4, scan 64 + golden 12: 15.5 -> 14.7 us a sweep, 17 controls 9.3 -> 8.8; 96^3 x
+// 64: 1646 -> 1596).  The row of the mass plane is read once, with the other terms
+// of the node: read again for the feet's cells it was a trip to memory of its own.
+template <int kMode, bool kOne, bool kBatch>
+__device__ inline void fast_node(ConstArgs p, int t, bool live, uint32_t packed, float4* lds, bool resid, NodeSums& S) {
+  const SweepArgs a = sweep_args<kBatch>(anew(p));
   NodeTerms T;
-  const int j = node_terms_tab(a, packed, T);
-  const float vin = (resid || kMode == 2) ? a.V_in[j] : 0.0f;
+  float4 m;
+  const int j = node_terms_tab(a, packed, T, m);
   constexpr bool kAngles = kOne && (kMode == 1 || kMode == 2);
   WaveAngles W;
   if constexpr (kAngles) load_angles(a, lds, W);
   FeetCells C;
-  feet_cells<kOne>(a, T, C);
+  feet_cells<kOne>(a, T, m, C);
   typename std::conditional<kOne, CellNode, FastNode>::type F;
   float qc;
   if constexpr (kOne) qc = cell_setup(a, T, C, F);
@@ -889,25 +955,28 @@ __device__ inline void fast_node(const SweepArgs& a, int t, uint32_t packed, flo
     if constexpr (kOne) return cell_q(F, sn, cs);
     else return fast_q(F, sn, cs);
   };
-  if constexpr (kAngles) store_angles(a, W);
+  const float vin = a.V_in[j];
+  const SweepArgs b = sweep_args<kBatch>(anew(p));
+  if constexpr (kAngles) store_angles(b, W);
   auto scan = [&](float& bq, int& bk) {
-    if constexpr (kAngles) scan_cell(a, F, W, bq, bk);
-    else scan_table(qf, a, bq, bk);
+    if constexpr (kAngles) scan_cell(b, F, W, bq, bk);
+    else scan_table(qf, b, bq, bk);
   };
   Choice ch;
-  search_node<kMode>(qf, scan, a, j, qc, vin, ch, S);
-  if (t >= a.n_free) {
+  search_node<kMode>(qf, scan, b, j, qc, vin, ch, S);
+  if (!live) {
     S = NodeSums();
     return;
   }
-  keep_incumbent(qf, a, j, qc, ch);
-  if (a.desc_code || a.desc16 || a.desc_pk) {
+  const SweepArgs c = sweep_args<kBatch>(anew(p));
+  keep_incumbent(qf, c, j, qc, ch);
+  if (c.desc_code || c.desc16 || c.desc_pk) {
     // formats by free-list position: the node's place in node order
-    const int at = a.desc_pk ? 0 : (t & ~(kOrderChunk - 1)) + a.sweep_pos[t];
-    if (kOne) write_desc_cell(a, at, j, T, C, ch);
-    else write_desc(a, at, j, T, ch);
+    const int at = c.desc_pk ? 0 : (t & ~(kOrderChunk - 1)) + c.sweep_pos[t];
+    if (kOne) write_desc_cell(c, at, j, T, C, ch);
+    else write_desc(c, at, j, T, ch);
   }
-  store_node(a, j, vin, ch, resid, S);
+  store_node(c, j, vin, ch, resid, S);
 }
 
 // A workgroup's nodes, one per thread.  A wave whose nodes are all one-cell
@@ -921,8 +990,10 @@ __device__ inline void fast_node(const SweepArgs& a, int t, uint32_t packed, flo
 // the kernel instead (listing the others in LDS, per workgroup or per wave, and
 // running them together) took 1.96-2.8 ms: the second phase leaves lanes and
 // waves idle.
-template <int kMode>
-__device__ inline void sweep_nodes(const SweepArgs& a, int tile, float4* lds, bool resid, NodeSums& S) {
+template <int kMode, bool kBatch>
+__device__ inline void sweep_nodes(ConstArgs p, int tile, float4* lds, bool resid, NodeSums& S) {
+  const SweepArgs a = sweep_args<kBatch>(p);
+  touch_args(p);
   const int bd = (int)blockDim.x, tid = (int)threadIdx.x;
   const int first = __builtin_amdgcn_readfirstlane(tile * bd + (tid & ~63));
   const int t = first + (tid & 63), in_wave = min(64, a.n_free - first);
@@ -930,10 +1001,12 @@ __device__ inline void sweep_nodes(const SweepArgs& a, int tile, float4* lds, bo
   // the node and the kind of its wave are loaded together: a sweep of few
   // controls waits on memory, not on arithmetic.  Lanes beyond the list's end
   // go with its last node and store nothing.
-  const uint32_t packed = a.sweep_node[min(t, a.n_free - 1)];
-  const bool one = (first & (kOrderChunk - 1)) + in_wave <= a.one_cell[first / kOrderChunk];
-  if (one) fast_node<kMode, true>(a, t, packed, lds, resid, S);
-  else fast_node<kMode, false>(a, t, packed, lds, resid, S);
+  const bool live = t < a.n_free;
+  const uint32_t packed = a.sweep_node[live ? t : a.n_free - 1];
+  typedef const __attribute__((address_space(4))) int* ConstCount;
+  const bool one = (first & (kOrderChunk - 1)) + in_wave <= ((ConstCount)a.one_cell)[first / kOrderChunk];
+  if (one) fast_node<kMode, true, kBatch>(p, t, live, packed, lds, resid, S);
+  else fast_node<kMode, false, kBatch>(p, t, live, packed, lds, resid, S);
 }
 
 // Dynamic LDS of sweep_nodes.
