@@ -35,7 +35,7 @@ struct dpo_ctx {
   uint32_t* free_node = nullptr;  // packed coordinates of the free nodes, node order
   uint32_t* sweep_node = nullptr;  // the free list in the factorised sweeps' order (see SweepArgs)
   uint16_t* sweep_pos = nullptr;
-  int* one_cell = nullptr;
+  unsigned long long* one_cell = nullptr;
   double* rinv = nullptr;         // 1/r per r node (FP64)
   float* gtab = nullptr;          // [2][n_m]: thrust displacement per unit sin (v_r) / cos (v_t)
   char* node_tab = nullptr;       // tables of the node terms (see SweepArgs)
@@ -994,7 +994,7 @@ int dpo_create(const dpo_grid* grid, const dpo_problem* prob, const dpo_search* 
     if (hipMalloc(&c->node_tab, bytes) != hipSuccess ||
         (c->fast_ok && (hipMalloc(&c->sweep_node, sizeof(uint32_t) * n) != hipSuccess ||
                         hipMalloc(&c->sweep_pos, sizeof(uint16_t) * n) != hipSuccess ||
-                        hipMalloc(&c->one_cell, sizeof(int) * blocks_for(n, kOrderChunk)) != hipSuccess))) {
+                        hipMalloc(&c->one_cell, sizeof(unsigned long long) * blocks_for(n, kOrderChunk)) != hipSuccess))) {
       c->err = "device allocation failed in dpo_create";
       return cleanup(DPO_ENOMEM);
     }

@@ -2,6 +2,7 @@
 #pragma once
 
 #include "dpo_device.h"
+#include "dpo_order.h"
 
 namespace dpo {
 
@@ -25,11 +26,12 @@ struct SweepArgs {
   const uint32_t* free_node;  // packed coordinates (8 bits per axis, r lowest) of the free nodes
   int n_free;
   // factorised sweeps: the free list reordered within chunks of kOrderChunk
-  // entries, of which the first one_cell[k] of chunk k are nodes whose thrust
-  // feet share one cell; sweep_pos: an entry's place in node order in its chunk
+  // entries into waves of nodes whose thrust feet share one cell and others; bit w
+  // of one_cell[k]: wave w of chunk k is of the first kind; sweep_pos: an entry's
+  // place in node order in its chunk
   const uint32_t* sweep_node;
   const uint16_t* sweep_pos;
-  const int* one_cell;
+  const unsigned long long* one_cell;
   // tables of the node terms (see node_terms_at): FP64 1/r per r node; drift along r
   // per v_r node, along v_r per (v_t, r), along v_t times r per (v_t, v_r) in
   // FP64, along theta (crown, else null) per (v_t, r); per mass plane the thrust
@@ -85,8 +87,6 @@ struct SweepArgs {
   double w_time, w_fuel, lambda;
 };
 
-constexpr int kOrderChunk = 4096;  // entries of the free list ordered together (a multiple of 64)
-
 inline int blocks_for(long long n, int per = kBlock) { return (int)((n + per - 1) / per); }
 
 constexpr uint16_t kDescOut = 1u << 12;
@@ -140,8 +140,8 @@ hipError_t launch_compact(const Grid& G, const uint8_t* kind, int N, int* counts
 // formulas; g1tab, g2tab: thrust displacement per mass plane.
 hipError_t launch_node_tables(const SweepArgs& a, const float* g1tab, const float* g2tab, hipStream_t s);
 // Fills sweep_node, sweep_pos and one_cell (see SweepArgs) from the free list.
-hipError_t launch_order_free(const SweepArgs& a, uint32_t* sweep_node, uint16_t* sweep_pos, int* one_cell,
-                             hipStream_t s);
+hipError_t launch_order_free(const SweepArgs& a, uint32_t* sweep_node, uint16_t* sweep_pos,
+                             unsigned long long* one_cell, hipStream_t s);
 hipError_t launch_init_value(const uint8_t* kind, float M, float* V, int N, hipStream_t s);
 // Direct-path sweep; mode 0 table, 1 scan + golden, 2 seeded, 3 table walk
 // (the integrator comes from a.P.heun).

@@ -165,18 +165,22 @@ __device__ inline void node_heun(const SweepArgs& a, const int i[4], HeunTerms& 
 // Order of the free list for the factorised sweeps.  Whether a node's thrust
 // feet share one cell depends on the grid and the physics alone, and the 64
 // consecutive nodes of a wave nearly always hold one whose feet do not (95 %
-// of the waves at 5-15 % of the nodes), so that every wave would run the
+// of the waves at 2-15 % of the nodes), so that every wave would run the
 // general form of the search.  Within chunks of kOrderChunk entries (the
-// value rows of a chunk stay in one XCD's L2) the one-cell nodes come first.
+// value rows of a chunk stay in one XCD's L2) the one-cell nodes fill waves of
+// their own, placed by place_waves; one_cell: a bit per wave of the chunk.
 __global__ __launch_bounds__(kBlock) void k_order_free(SweepArgs a, uint32_t* __restrict__ sweep_node,
-                                                       uint16_t* __restrict__ sweep_pos, int* __restrict__ one_cell) {
-  __shared__ int wave_one[kBlock / 64], wave_rest[kBlock / 64];
+                                                       uint16_t* __restrict__ sweep_pos,
+                                                       unsigned long long* __restrict__ one_cell) {
+  constexpr int kWaves = kBlock / 64, kSlots = kOrderChunk / 64;
+  static_assert(kSlots == 64, "one bit per wave of a chunk");
+  __shared__ int wave_one[kWaves], wave_rest[kWaves], slot_of[kSlots];
   const int base = blockIdx.x * kOrderChunk, n = min(kOrderChunk, a.n_free - base);
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   // one contiguous slice of the chunk per wave
-  const int slice = kOrderChunk / (kBlock / 64), lo = wave * slice, hi = min(lo + slice, n);
+  const int slice = kOrderChunk / kWaves, lo = wave * slice, hi = min(lo + slice, n);
   int ones = 0, rest = 0;
-  unsigned long long kinds[kOrderChunk / kBlock];
+  unsigned long long kinds[kSlots / kWaves];
 #pragma unroll
   for (int r = 0; r < slice / 64; r++) {
     const int e = lo + r * 64 + lane;
@@ -200,11 +204,12 @@ __global__ __launch_bounds__(kBlock) void k_order_free(SweepArgs a, uint32_t* __
   __syncthreads();
   if (threadIdx.x == 0) {
     int total = 0;
-    for (int w = 0; w < kBlock / 64; w++) total += wave_one[w];
-    one_cell[blockIdx.x] = total;
+    for (int w = 0; w < kWaves; w++) total += wave_one[w];
+    one_cell[blockIdx.x] = place_waves(n, total, blockIdx.x, slot_of);
   }
+  __syncthreads();
   int at_one = 0, at_rest = 0;
-  for (int w = 0; w < kBlock / 64; w++) {
+  for (int w = 0; w < kWaves; w++) {
     at_rest += wave_one[w];
     if (w < wave) {
       at_one += wave_one[w];
@@ -218,7 +223,8 @@ __global__ __launch_bounds__(kBlock) void k_order_free(SweepArgs a, uint32_t* __
     const bool one = (kinds[r] >> lane) & 1ull;
     const unsigned long long others = __ballot(e < hi && !one);
     if (e < hi) {
-      const int to = base + (one ? at_one + __popcll(kinds[r] & below) : at_rest + __popcll(others & below));
+      const int place = one ? at_one + __popcll(kinds[r] & below) : at_rest + __popcll(others & below);
+      const int to = base + slot_of[place >> 6] * 64 + (place & 63);
       sweep_node[to] = a.free_node[base + e];
       sweep_pos[to] = (uint16_t)e;
     }
@@ -977,8 +983,8 @@ hipError_t launch_node_tables(const SweepArgs& a, const float* g1tab, const floa
   DPO_LAUNCH(k_node_tables, blocks_for(most), kBlock, s, a, g1tab, g2tab);
 }
 
-hipError_t launch_order_free(const SweepArgs& a, uint32_t* sweep_node, uint16_t* sweep_pos, int* one_cell,
-                             hipStream_t s) {
+hipError_t launch_order_free(const SweepArgs& a, uint32_t* sweep_node, uint16_t* sweep_pos,
+                             unsigned long long* one_cell, hipStream_t s) {
   DPO_LAUNCH(k_order_free, blocks_for(a.n_free, kOrderChunk), kBlock, s, a, sweep_node, sweep_pos, one_cell);
 }
 

@@ -996,15 +996,15 @@ __device__ inline void sweep_nodes(ConstArgs p, int tile, float4* lds, bool resi
   touch_args(p);
   const int bd = (int)blockDim.x, tid = (int)threadIdx.x;
   const int first = __builtin_amdgcn_readfirstlane(tile * bd + (tid & ~63));
-  const int t = first + (tid & 63), in_wave = min(64, a.n_free - first);
-  if (in_wave <= 0) return;
+  const int t = first + (tid & 63);
+  if (first >= a.n_free) return;
   // the node and the kind of its wave are loaded together: a sweep of few
   // controls waits on memory, not on arithmetic.  Lanes beyond the list's end
   // go with its last node and store nothing.
   const bool live = t < a.n_free;
   const uint32_t packed = a.sweep_node[live ? t : a.n_free - 1];
-  typedef const __attribute__((address_space(4))) int* ConstCount;
-  const bool one = (first & (kOrderChunk - 1)) + in_wave <= ((ConstCount)a.one_cell)[first / kOrderChunk];
+  typedef const __attribute__((address_space(4))) unsigned long long* ConstBits;
+  const bool one = (((ConstBits)a.one_cell)[first / kOrderChunk] >> ((first / 64) & 63)) & 1;
   if (one) fast_node<kMode, true, kBatch>(p, t, live, packed, lds, resid, S);
   else fast_node<kMode, false, kBatch>(p, t, live, packed, lds, resid, S);
 }
