@@ -246,11 +246,9 @@ __device__ inline float cached_value(const CornerCache& cc, const float t[4]) {
 // < f + 1 on an axis means that floor(off) is the cached one); any other is looked
 // up by foot_cell, whatever its arrangement.  Along the periodic axis a foot
 // within 2e-5 of the cell's upper face is looked up too (there the wrap's
-// quotient may round up).  So is a foot that is not a number along v_r or v_t (a
-// proposed or kept angle that is not finite): the clamp to the faces would make
-// it the lower face, and only the look-up, which clamps numbers alone, answers M.
-// (The Heun foot of such an angle is not a number along r either.)
-template <bool kHeun, bool kCrown>
+// quotient may round up).  A cache that may not keep cells (see cache_init) looks
+// every foot up.
+template <bool kCrown>
 __device__ inline float cached_interp(const float* __restrict__ V, const Grid& G, const int i[4], const float off[4],
                                       float M, CornerCache& cc) {
   float o1 = off[1], o2 = off[2];
@@ -266,8 +264,7 @@ __device__ inline float cached_interp(const float* __restrict__ V, const Grid& G
   if (kCrown) t[3] = (((float)i[3] + off[3]) - cc.wrap) - cc.f[3];
   else t[3] = off[3] - cc.f[3];
   const float low = fminf(fminf(t[0], t[1]), fminf(t[2], t[3]));
-  const bool in = low >= 0.0f && t[3] + near_top < 1.0f && off[0] < cc.top[0] && o1 < cc.top[1] && o2 < cc.top[2] &&
-                  !(kCrown && !kHeun && __builtin_isunordered(off[1], off[2]));
+  const bool in = low >= 0.0f && t[3] + near_top < 1.0f && off[0] < cc.top[0] && o1 < cc.top[1] && o2 < cc.top[2];
   if (!in) {
     // leaving the domain along r: the same answer for every control of most such nodes
     if (!(off[0] >= (float)(-i[0]) && off[0] <= (float)(G.n[0] - 1 - i[0]))) return M;
@@ -304,7 +301,7 @@ struct KeyedCorners {
   CornerCache c;  // only c.v is used
 };
 
-template <bool kHeun, bool kCrown>
+template <bool kCrown>
 __device__ inline float cached_interp(const float* __restrict__ V, const Grid& G, const int i[4], const float off[4],
                                       float M, KeyedCorners& kc) {
   int base[4];
@@ -443,11 +440,14 @@ __device__ inline float q_step(const float* __restrict__ V, const Grid& G, const
   return fmaf(P.gamma, interp_off<kSnap>(V, G, T.i, off, P.M), (thr ? P.q_thr : P.q_coast) + qx);
 }
 
-// An empty cache.  keep: cells may be kept (every term of the node's
-// displacements is finite and moderate, and so is every foot of a finite angle).
-__device__ inline void cache_init(const NodeTerms& T, const HeunTerms& H, bool heun, CornerCache& cc) {
+// An empty cache.  angles: every angle that the node will be asked for is finite.
+// keep: cells may be kept, so is every term of the node's displacements and of a
+// moderate size.  A foot that is not a number must not meet the fast test: the
+// crown's clamp to the velocity faces would make it the lower face, and only the
+// look-up, which clamps numbers alone, answers M.
+__device__ inline void cache_init(const NodeTerms& T, const HeunTerms& H, bool heun, bool angles, CornerCache& cc) {
   const float big = 1e6f;
-  bool keep = true;
+  bool keep = angles;
   for (int k = 0; k < 4; k++) keep = keep && fabsf(T.drift[k]) < big;
   keep = keep && fabsf(T.g1) < big && fabsf(T.g2) < big && fabsf(T.gm) < big;
   if (heun && H.orbit) {
@@ -462,7 +462,7 @@ __device__ inline void cache_init(const NodeTerms& T, const HeunTerms& H, bool h
   cc.top[0] = cc.top[1] = cc.top[2] = 0.0f;
 }
 
-__device__ inline void cache_init(const NodeTerms&, const HeunTerms&, bool, KeyedCorners& kc) { kc.key = -1; }
+__device__ inline void cache_init(const NodeTerms&, const HeunTerms&, bool, bool, KeyedCorners& kc) { kc.key = -1; }
 
 // q_step through a node's cache.
 template <bool kHeun, bool kCrown, class Cache>
@@ -470,7 +470,7 @@ __device__ inline float q_step_cached(const float* __restrict__ V, const Grid& G
                                       const HeunTerms& H, int thr, float sn, float cs, float qx, Cache& cc) {
   float off[4];
   foot_off<kHeun, kCrown>(T, H, thr, sn, cs, off);
-  return fmaf(P.gamma, cached_interp<kHeun, kCrown>(V, G, T.i, off, P.M, cc), (thr ? P.q_thr : P.q_coast) + qx);
+  return fmaf(P.gamma, cached_interp<kCrown>(V, G, T.i, off, P.M, cc), (thr ? P.q_thr : P.q_coast) + qx);
 }
 
 // The crown problem's orbital-element running cost at a physical state x =

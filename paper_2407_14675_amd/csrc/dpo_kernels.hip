@@ -267,7 +267,13 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(kKeyed ?
     const float* __restrict__ V = a.V_in;
     const float qx = a.qnode ? a.qnode[j] : 0.0f;
     typename std::conditional<kKeyed, KeyedCorners, CornerCache>::type cc;
-    cache_init(T, H, kHeun, cc);
+    // the angles that do not come from the table
+    bool angles = true;
+    if (kCrown && !kKeyed) {
+      if (kMode == 2) angles = isfinite(a.seed[j]);
+      if (a.pol_ang_in) angles = angles && isfinite(a.pol_ang_in[j]);
+    }
+    cache_init(T, H, kHeun, angles, cc);
     auto qf = [&](float sn, float cs) { return q_step_cached<kHeun, kCrown>(V, a.G, a.P, T, H, 1, sn, cs, qx, cc); };
     const float qc = q_step_cached<kHeun, kCrown>(V, a.G, a.P, T, H, 0, 0.0f, 1.0f, qx, cc);
     const float vin = V[j];
