@@ -41,6 +41,7 @@ struct dpo_ctx {
   char* node_tab = nullptr;       // tables of the node terms (see SweepArgs)
   double c0 = 0, c1 = 0, c2 = 0;  // dt/h for r, v_r, v_t
   float gm = 0;                   // thrust displacement along m
+  float reach = 0;                // longest thrust displacement along v_r or v_t, cells
   bool fast_ok = false;           // the factorised thrust kernel applies
   int path = 0;                   // 0 auto, 1 direct, 2 fast
   BrickPlan brick{};              // frozen-policy sweep with LDS value bricks (dense grids)
@@ -607,7 +608,7 @@ int sweep_full(dpo_ctx* c, const float* Vin, float* Vout, float* ang, uint8_t* t
   }
   hipError_t e;
   if (use_fast(c)) e = launch_sweep_fast(a, mode, c->block, s);
-  else e = launch_sweep_direct(a, mode, s);
+  else e = launch_sweep_direct(a, mode, c->reach, s);
   c->last_blocks = blocks_for(c->n_free, use_fast(c) ? c->block : kBlock);
   if (e != hipSuccess) return hip_fail(c, e, "bellman sweep launch");
   return DPO_OK;
@@ -629,7 +630,7 @@ int sweep_seeded(dpo_ctx* c, const float* Vin, float* Vout, float* ang, uint8_t*
   else c->desc_valid = false;
   if (a.n_free == 0) return DPO_OK;
   if (!use_fast(c)) {
-    hipError_t e = launch_sweep_direct(a, 2, s);
+    hipError_t e = launch_sweep_direct(a, 2, c->reach, s);
     c->last_blocks = blocks_for(c->n_free, kBlock);
     if (e != hipSuccess) return hip_fail(c, e, "seeded sweep launch");
     return DPO_OK;
@@ -948,6 +949,7 @@ int dpo_create(const dpo_grid* grid, const dpo_problem* prob, const dpo_search* 
     c->c2 = prob->dt * c->G.inv_h[2];
     const double gm = prob->model == DPO_MODEL_ORBIT ? -prob->dt * prob->mdot * c->G.inv_h[3] : 0.0;
     c->gm = (float)gm;
+    c->reach = (float)gmax;
     // the factorised thrust kernel needs every thrust foot of a node within two
     // cells per moving axis and within one m cell
     c->fast_ok = gmax < 0.45 && gm > -1.0 && gm <= 0.0 && prob->integrator == DPO_STEP_EULER && !crown;

@@ -145,7 +145,7 @@ hipError_t launch_order_free(const SweepArgs& a, uint32_t* sweep_node, uint16_t*
 hipError_t launch_init_value(const uint8_t* kind, float M, float* V, int N, hipStream_t s);
 // Direct-path sweep; mode 0 table, 1 scan + golden, 2 seeded, 3 table walk
 // (the integrator comes from a.P.heun).
-hipError_t launch_sweep_direct(const SweepArgs& a, int mode, hipStream_t s);
+hipError_t launch_sweep_direct(const SweepArgs& a, int mode, float reach, hipStream_t s);
 hipError_t launch_policy_eval(const SweepArgs& a, bool want_resid, hipStream_t s);
 // crown problem: qnode[j] = dt * running cost at node j (FP64, rounded)
 hipError_t launch_node_cost(const Grid& G, const Phys& P, float* qnode, int N, hipStream_t s);

@@ -7,6 +7,7 @@
 // minimisation by tabulation and golden section, feedback eq:feed).
 #include <algorithm>
 
+#include "dpo_forms.h"
 #include "dpo_search.h"
 
 namespace dpo {
@@ -242,17 +243,16 @@ __global__ __launch_bounds__(kBlock) void k_init_value(const uint8_t* __restrict
 // --------------------------------------------------------------- a2..a8
 // ---- direct path: every evaluation forms its foot; cell and corners come
 // from the node's cache unless the foot leaves the cell of the previous
-// evaluation (CornerCache).  Used for any problem and for the Heun foot; the
-// fast path below covers the orbit workloads with the Euler foot.  Bound by
-// vector instruction issue: looking every foot's cell up (four axes with
-// their faces, the periodic one with a division) was half of the instructions.
-// Example 1 (110 x 30 x 30 x 30, 73 controls, Heun foot): 589 -> 394 us, 11,200
-// -> 6,600 vector instructions per wave; five waves per SIMD at 96 registers (four at 108:
-// 408 us, six with spills: 0.7 ms).  Ordering the nodes as for the factorised
-// sweeps took 414 us: too few nodes here have feet in several cells.
-// kKeyed: only the corners are kept (KeyedCorners), and every evaluation looks its
-// cell up; the form for the Heun foot on grids too small to hide a look-up
-// behind other waves (kKeyedNodes).
+// evaluation (CornerCache), or, kKeyed, the corners alone are kept and every
+// evaluation looks its cell up (KeyedCorners); keep_cells says which.  Used for any
+// problem and for the Heun foot; the fast path below covers the orbit workloads
+// with the Euler foot.  Bound by vector instruction issue: looking every foot's
+// cell up (four axes with their faces, the periodic one with a division) was half
+// of the instructions.  Example 1 (110 x 30 x 30 x 30, 73 controls, Heun foot): 589
+// -> 394 us, 11,200 -> 6,600 vector instructions per wave, at five waves per SIMD
+// and 96 registers with 11 more spilled (48 bytes a lane); four waves at 108
+// registers and no spill: 425 us, six with more spills 0.7 ms.  Ordering the nodes as for the
+// factorised sweeps took 414 us: too few nodes here have feet in several cells.
 template <int kMode, bool kHeun, bool kCrown, bool kKeyed>
 __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(kKeyed ? 4 : 5))) void k_sweep_direct(SweepArgs a) {
   const int tile = xcd_tile(blockIdx.x, gridDim.x);
@@ -999,29 +999,30 @@ hipError_t launch_init_value(const uint8_t* kind, float M, float* V, int N, hipS
 }
 
 namespace {
-template <bool kHeun, bool kCrown, bool kKeyed>
-hipError_t sweep_direct(const SweepArgs& a, int mode, hipStream_t s) {
+template <bool kHeun, bool kCrown>
+hipError_t sweep_direct(const SweepArgs& a, int mode, bool cells, hipStream_t s) {
   const int nb = blocks_for(a.n_free);
-  if (mode == 0) DPO_LAUNCH((k_sweep_direct<0, kHeun, kCrown, kKeyed>), nb, kBlock, s, a);
-  if (mode == 1) DPO_LAUNCH((k_sweep_direct<1, kHeun, kCrown, kKeyed>), nb, kBlock, s, a);
-  if (mode == 2) DPO_LAUNCH((k_sweep_direct<2, kHeun, kCrown, kKeyed>), nb, kBlock, s, a);
-  DPO_LAUNCH((k_sweep_direct<3, kHeun, kCrown, kKeyed>), nb, kBlock, s, a);
+  if (cells) {
+    if (mode == 0) DPO_LAUNCH((k_sweep_direct<0, kHeun, kCrown, false>), nb, kBlock, s, a);
+    if constexpr (!kHeun) {
+      if (mode == 1) DPO_LAUNCH((k_sweep_direct<1, kHeun, kCrown, false>), nb, kBlock, s, a);
+      if (mode == 2) DPO_LAUNCH((k_sweep_direct<2, kHeun, kCrown, false>), nb, kBlock, s, a);
+      if constexpr (kCrown)
+        if (mode == 3) DPO_LAUNCH((k_sweep_direct<3, kHeun, kCrown, false>), nb, kBlock, s, a);
+    }
+  }
+  constexpr bool kOwn = kHeun && kCrown;  // the crown's Euler foot is formed as any other
+  if (mode == 0) DPO_LAUNCH((k_sweep_direct<0, kHeun, kOwn, true>), nb, kBlock, s, a);
+  if (mode == 1) DPO_LAUNCH((k_sweep_direct<1, kHeun, kOwn, true>), nb, kBlock, s, a);
+  if (mode == 2) DPO_LAUNCH((k_sweep_direct<2, kHeun, kOwn, true>), nb, kBlock, s, a);
+  DPO_LAUNCH((k_sweep_direct<3, kHeun, kOwn, true>), nb, kBlock, s, a);
 }
 }  // namespace
 
-// Below one load of the chip at the cell cache's five waves per SIMD a Heun
-// sweep's waves wait for each look-up (scratch and gathers) with nothing beside
-// them.  Heun foot, 72 angles, cell cache / keyed corners: 25 x 15^3 60 / 51 us,
-// 40 x 20^3 94 / 83, 60 x 25^3 179 / 197, 110 x 30^3 394 / 540; the Euler foot is
-// the faster with the cell cache at every size (25 x 15^3: 30 / 38).
-constexpr int kKeyedNodes = 5 * 64 * 1024;
-
-hipError_t launch_sweep_direct(const SweepArgs& a, int mode, hipStream_t s) {
-  if (a.P.heun && a.n_free < kKeyedNodes)
-    return a.P.model == 2 ? sweep_direct<true, true, true>(a, mode, s) : sweep_direct<true, false, true>(a, mode, s);
-  if (a.P.model == 2)
-    return a.P.heun ? sweep_direct<true, true, false>(a, mode, s) : sweep_direct<false, true, false>(a, mode, s);
-  return a.P.heun ? sweep_direct<true, false, false>(a, mode, s) : sweep_direct<false, false, false>(a, mode, s);
+hipError_t launch_sweep_direct(const SweepArgs& a, int mode, float reach, hipStream_t s) {
+  const bool cells = keep_cells(mode, a.P.model == 2, a.P.heun != 0, a.n_ang, a.n_free, reach);
+  if (a.P.model == 2) return a.P.heun ? sweep_direct<true, true>(a, mode, cells, s) : sweep_direct<false, true>(a, mode, cells, s);
+  return a.P.heun ? sweep_direct<true, false>(a, mode, cells, s) : sweep_direct<false, false>(a, mode, cells, s);
 }
 
 hipError_t launch_node_cost(const Grid& G, const Phys& P, float* qnode, int N, hipStream_t s) {
