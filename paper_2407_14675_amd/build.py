@@ -11,7 +11,7 @@ ROOT = os.path.dirname(HERE)
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libdpo.so")
 SOURCES = ["dpo_kernels.hip", "dpo_batch.hip", "dpo_mlp.hip", "dpo_krylov.hip", "dpo_ceiling.hip", "dpo_brick.hip", "dpo_api.hip"]
-HEADERS = ["dpo_device.h", "dpo_forms.h", "dpo_order.h", "dpo_kernels.h", "dpo_search.h", "dpo_mlp.h", "dpo_krylov.h"]
+HEADERS = ["dpo_device.h", "dpo_forms.h", "dpo_order.h", "dpo_kernels.h", "dpo_search.h", "dpo_window.h", "dpo_mlp.h", "dpo_krylov.h"]
 
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 FLAGS = [

@@ -18,6 +18,7 @@
 
 #include "../../include/dpo.h"
 #include "dpo_kernels.h"
+#include "dpo_window.h"
 #include "dpo_mlp.h"
 #include "dpo_krylov.h"
 
@@ -225,10 +226,6 @@ Grid make_grid(const dpo_grid& g, bool periodic3 = false) {
   G.st[3] = g.n[0] * g.n[1] * g.n[2];
   return G;
 }
-
-// Constants of scan_window for a table of K angles, the first rounded up.
-float scan_y0_for(int K) { return std::nextafterf((float)(1.0 - std::cos(3.14159265358979323846 / K)), 4.0f); }
-float scan_k_for(int K) { return (float)(K / (2.0 * 3.14159265358979323846)); }
 
 // The node-term tables lie one after another in one allocation, the widest
 // entries first; returns its size in bytes.

@@ -10,6 +10,7 @@
 #include <type_traits>
 
 #include "dpo_kernels.h"
+#include "dpo_window.h"
 
 namespace dpo {
 
@@ -626,21 +627,11 @@ __device__ inline float fast_setup(const SweepArgs& a, const NodeTerms& T, const
 
 
 // ---- nodes whose thrust feet all fall in one cell (one region along v_r and
-// one along v_t; 80-95 % of the nodes of the 96^3 x 64 and 48^4 workloads,
-// whose thrust moves a foot by 0.02-0.05 cell): the four coefficients of the
-// bilinear form stay in registers, 8 corner pairs are gathered instead of 18,
-// and an evaluation is 7 instructions with no region test and no LDS read.
-struct CellNode {
-  float g1, g2, d1, d2;
-  float x, y, z, w;  // Q = x + y dv + z dt + w dv dt
-};
-
-__device__ inline float cell_q(const CellNode& F, float sn, float cs) {
-  const float ov = fmaf(F.g1, sn, F.d1), ot = fmaf(F.g2, cs, F.d2);
-  const float dv = ov - F.d1, dt = ot - F.d2;
-  return fmaf(fmaf(F.w, dt, F.y), dv, fmaf(F.z, dt, F.x));
-}
-
+// one along v_t): 92 % of the nodes of the 96^3 x 64 problem, 88 % of 48^4, 82 to 99 %
+// of the sixteen batched problems.  The four coefficients of the bilinear form stay in
+// registers (CellNode), 8 corner pairs are gathered instead of 18, and an evaluation is
+// 7 instructions with no region test and no LDS read.
+//
 // Set-up of such a node: the operations of fast_setup on its one region pair,
 // in the same order, so the values are the same bit for bit.  Returns the
 // coast Q.
@@ -687,58 +678,6 @@ __device__ inline float cell_setup(const SweepArgs& a, const NodeTerms& T, const
   return fmaf(a.P.gamma, Ic, a.P.q_coast);
 }
 
-// The part of the table that can hold its minimum.  On one cell Q(u) = x +
-// b sin u + c cos u + d sin u cos u with b = y g1, c = z g2, d = w g1 g2, so
-// every tabulated Q is x - R cos(u - u*) up to E = |d|/2 plus the rounding of
-// the evaluation, R = hypot(b, c), u* = atan2(b, c) + pi.  The sample nearest
-// to u* lies within pi/K of it, so a sample farther than theta,
-//     1 - cos(theta) = 1 - cos(pi/K) + 2 E / R,
-// is above that one and cannot be the first minimum; the samples within theta are
-// evaluated exactly as the full scan evaluates them.  The number of samples
-// is at most kWindow, else 0 (the caller scans the whole table): nodes with R = 0,
-// non-finite or huge coefficients, and those so flat that the rounding of Q
-// hides the minimum.
-constexpr int kWindow = 24;
-
-__device__ inline int scan_window(const SweepArgs& a, const CellNode& F, int& k0) {
-  k0 = 0;
-  // all coefficients zero (a plateau): every sample has the same Q
-  if (F.y == 0.0f && F.z == 0.0f && F.w == 0.0f) return 1;
-  const float g1 = fabsf(F.g1), g2 = fabsf(F.g2);
-  const float b = F.y * F.g1, c = F.z * F.g2;
-  const float P = fmaf(fabsf(F.w), g2, fabsf(F.y)), Q = fmaf(fabsf(F.w), g1, fabsf(F.z));
-  // the largest |Q|; its unit in the last place bounds the half-units of the two
-  // outer operations, the foot's displacements are half a unit of drift and thrust off each
-  const float top = fmaf(P, g1, fmaf(Q, g2, fabsf(F.x)));
-  const float ulp = __int_as_float(__float_as_int(top) & 0x7f800000) * 1.1920929e-7f;
-  const float E = 1.05f * fmaf(0.5f * fabsf(F.w) * g1, g2,
-                               fmaf(5.9604645e-8f, fmaf(P, fmaf(6.0f, g1, fabsf(F.d1)), Q * fmaf(6.0f, g2, fabsf(F.d2))), ulp));
-  // the approximate root and reciprocals below are within 2e-7 of the exact ones, the
-  // table steps' margin of 0.02 and the 5 % on the rounding bound cover them
-  const float R = __builtin_amdgcn_sqrtf(fmaf(b, b, c * c));
-  // 1 - cos(theta) = 2 s^2 with s = sin(theta / 2); asin(s) <= s + (pi/2 - 1) s^3 on [0, 1]
-  const float h = fmaf(E, __builtin_amdgcn_rcpf(R), 0.5f * a.scan_y0);
-  if (!(R > 1e-18f && R < 1e18f && h <= 1.0f)) return 0;
-  const float s = __builtin_amdgcn_sqrtf(h);
-  const float wid = fmaf(2.0f * a.scan_k, s * fmaf(0.5708f, h, 1.0f), 0.02f);
-  // atan2(b, c) by Abramowitz and Stegun 4.4.49 (error below 1e-5 rad), in table steps:
-  // u* is entry K (atan2(b, c) / (2 pi)) mod K
-  const float ab = fabsf(b), ac = fabsf(c);
-  const float t = fminf(ab, ac) * __builtin_amdgcn_rcpf(fmaxf(ab, ac)), t2 = t * t;
-  float at = t * fmaf(t2, fmaf(t2, fmaf(t2, fmaf(t2, 0.0208351f, -0.0851330f), 0.1801410f), -0.3302995f), 0.9998660f);
-  at = ab > ac ? 1.5707964f - at : at;
-  at = c < 0.0f ? 3.1415927f - at : at;
-  at = b < 0.0f ? -at : at;
-  const float kc = at * a.scan_k;
-  const float lo = ceilf(kc - wid);
-  const int n = (int)(floorf(kc + wid) - lo) + 1;
-  if (n > kWindow || n > a.n_ang) return 0;
-  int k = (int)lo;
-  k = k < 0 ? k + a.n_ang : k;
-  k0 = k >= a.n_ang ? k - a.n_ang : k;
-  return n;
-}
-
 // The angle table as a one-cell wave reads it, each lane at its own entry: in
 // LDS, in the region pairs' place, which such a wave leaves unused (four runs
 // of 64 float4, a workgroup's width apart).  Every wave fills its own, so that
@@ -774,32 +713,15 @@ __device__ inline void store_angles(const SweepArgs& a, const WaveAngles& W) {
   __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
 }
 
-// The first minimum of the n table entries from k on, in table order also
-// where they wrap around the table's end; at(k): an entry's sin and cos.
-template <class At>
-__device__ inline void scan_entries(const SweepArgs& a, const CellNode& F, const At& at, int k, int n, float& bq, int& bk) {
-  bq = INFINITY;
-  bk = 0;
-  for (int i = 0; i < n; i++) {
-    const float2 sc = at(k);
-    const float q = cell_q(F, sc.x, sc.y);
-    if (q < bq || (q == bq && k < bk)) {
-      bq = q;
-      bk = k;
-    }
-    k = k + 1 == a.n_ang ? 0 : k + 1;
-  }
-}
-
 // scan_table for a one-cell node: the window where every active lane of the
 // wave has one (lanes in step through their own windows), else the whole
 // table.
 __device__ inline void scan_cell(const SweepArgs& a, const CellNode& F, const WaveAngles& W, float& bq, int& bk) {
   int k;
-  const int n = scan_window(a, F, k);
+  const int n = scan_window(F, a.n_ang, a.scan_y0, a.scan_k, k);
   if (!__all(n > 0)) scan_table([&](float sn, float cs) { return cell_q(F, sn, cs); }, a, bq, bk);
-  else if (a.n_ang <= kWaveAngles) scan_entries(a, F, [&](int e) { return W.at(e); }, k, n, bq, bk);
-  else scan_entries(a, F, [&](int e) { return make_float2(a.tab_sin[e], a.tab_cos[e]); }, k, n, bq, bk);
+  else if (a.n_ang <= kWaveAngles) scan_entries(F, a.n_ang, [&](int e) { return W.at(e); }, k, n, bq, bk);
+  else scan_entries(F, a.n_ang, [&](int e) { return make_float2(a.tab_sin[e], a.tab_cos[e]); }, k, n, bq, bk);
 }
 
 // write_desc for a one-cell node: the cell of every foot is known, and its
