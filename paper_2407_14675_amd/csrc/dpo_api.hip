@@ -14,6 +14,7 @@
 #include <cstring>
 #include <mutex>
 #include <string>
+#include <type_traits>
 #include <vector>
 
 #include "../../include/dpo.h"
@@ -32,6 +33,7 @@ struct dpo_ctx {
   Phys P;
   TargetBox tb;
   int64_t N = 0, n_free = 0;
+  char* arrays = nullptr;  // one allocation: kind to node_tab below and resid (see context_arrays)
   uint8_t* kind = nullptr;
   uint32_t* free_node = nullptr;  // packed coordinates of the free nodes, node order
   uint32_t* sweep_node = nullptr;  // the free list in the factorised sweeps' order (see SweepArgs)
@@ -243,6 +245,37 @@ size_t node_table_pointers(const dpo_ctx* c, SweepArgs& a) {
   a.drift0 = reinterpret_cast<const float*>(take(sizeof(float) * n[1]));
   a.drift3 = c->P.model == DPO_MODEL_CROWN ? reinterpret_cast<const float*>(take(sizeof(float) * n[0] * n[2])) : nullptr;
   return (size_t)(p - c->node_tab);
+}
+
+// The arrays that a context holds from its creation on lie in one allocation:
+// each one of its own costs up to 0.1 ms to make and to give back.  Sets their
+// pointers from c->arrays and returns the bytes; counts, offsets: scratch of the free
+// list's compaction.
+size_t context_arrays(dpo_ctx* c, int** counts, int** offsets) {
+  size_t at = 0;
+  auto take = [&](auto*& p, size_t n) {
+    at = (at + 255) & ~(size_t)255;
+    p = reinterpret_cast<std::remove_reference_t<decltype(p)>>(c->arrays + at);
+    at += n * sizeof(*p);
+  };
+  const size_t N = (size_t)c->N, chunks = (size_t)compact_chunks((int)c->N);
+  SweepArgs a;
+  c->node_tab = nullptr;
+  const size_t tables = node_table_pointers(c, a);
+  take(c->rinv, c->grid.n[0]);
+  take(c->gtab, 2 * (size_t)c->grid.n[3]);
+  take(c->node_tab, tables);
+  take(c->resid, kPartial);
+  take(*counts, chunks);
+  take(*offsets, chunks + 1);
+  take(c->kind, N);
+  take(c->free_node, N);
+  if (c->fast_ok) {
+    take(c->sweep_node, N);
+    take(c->sweep_pos, N);
+    take(c->one_cell, blocks_for(c->N, kOrderChunk));
+  }
+  return at;
 }
 
 SweepArgs base_args(const dpo_ctx* c) {
@@ -906,22 +939,12 @@ int dpo_create(const dpo_grid* grid, const dpo_problem* prob, const dpo_search* 
   int* offsets = nullptr;
   const int nch = compact_chunks(N);
   auto cleanup = [&](int code) {
-    if (counts) hipFree(counts);
-    if (offsets) hipFree(offsets);
     if (code != DPO_OK) {
       g_err = c->err;
       dpo_destroy(c);
     }
     return code;
   };
-  if (hipMalloc(&c->kind, (size_t)N) != hipSuccess || hipMalloc(&c->free_node, sizeof(uint32_t) * (size_t)N) != hipSuccess ||
-      hipMalloc(&c->rinv, sizeof(double) * grid->n[0]) != hipSuccess ||
-      hipMalloc(&c->gtab, sizeof(float) * 2 * grid->n[3]) != hipSuccess ||
-      hipMalloc(&counts, sizeof(int) * nch) != hipSuccess || hipMalloc(&offsets, sizeof(int) * (nch + 1)) != hipSuccess ||
-      hipMalloc(&c->resid, sizeof(double) * kPartial) != hipSuccess) {
-    c->err = "device allocation failed in dpo_create";
-    return cleanup(DPO_ENOMEM);
-  }
   // Per-axis tables: 1/r per r node (FP64), thrust displacement per m plane.
   {
     std::vector<double> rinv(grid->n[0]);
@@ -950,6 +973,11 @@ int dpo_create(const dpo_grid* grid, const dpo_problem* prob, const dpo_search* 
     // the factorised thrust kernel needs every thrust foot of a node within two
     // cells per moving axis and within one m cell
     c->fast_ok = gmax < 0.45 && gm > -1.0 && gm <= 0.0 && prob->integrator == DPO_STEP_EULER && !crown;
+    if (hipMalloc(&c->arrays, context_arrays(c, &counts, &offsets)) != hipSuccess) {
+      c->err = "device allocation failed in dpo_create";
+      return cleanup(DPO_ENOMEM);
+    }
+    context_arrays(c, &counts, &offsets);
     plan_brick(c);
     hipError_t e1 = hipMemcpy(c->rinv, rinv.data(), sizeof(double) * rinv.size(), hipMemcpyHostToDevice);
     hipError_t e2 = hipMemcpy(c->gtab, gt.data(), sizeof(float) * gt.size(), hipMemcpyHostToDevice);
@@ -988,19 +1016,10 @@ int dpo_create(const dpo_grid* grid, const dpo_problem* prob, const dpo_search* 
   }
   if ((rc = upload_table(c)) != DPO_OK) return cleanup(rc);
   {
-    SweepArgs a;
-    const size_t bytes = node_table_pointers(c, a), n = (size_t)std::max(1, total);
-    if (hipMalloc(&c->node_tab, bytes) != hipSuccess ||
-        (c->fast_ok && (hipMalloc(&c->sweep_node, sizeof(uint32_t) * n) != hipSuccess ||
-                        hipMalloc(&c->sweep_pos, sizeof(uint16_t) * n) != hipSuccess ||
-                        hipMalloc(&c->one_cell, sizeof(unsigned long long) * blocks_for(n, kOrderChunk)) != hipSuccess))) {
-      c->err = "device allocation failed in dpo_create";
-      return cleanup(DPO_ENOMEM);
-    }
-    a = base_args(c);
+    const SweepArgs a = base_args(c);
     e = launch_node_tables(a, c->gtab, c->gtab + grid->n[3], nullptr);
     if (e == hipSuccess && c->fast_ok && total > 0) e = launch_order_free(a, c->sweep_node, c->sweep_pos, c->one_cell, nullptr);
-    if (e == hipSuccess) e = hipDeviceSynchronize();
+    if (e == hipSuccess) e = hipStreamSynchronize(nullptr);
     if (e != hipSuccess) {
       c->err = std::string("dpo_create: ") + hipGetErrorString(e);
       return cleanup(DPO_EHIP);
@@ -1012,19 +1031,11 @@ int dpo_create(const dpo_grid* grid, const dpo_problem* prob, const dpo_search* 
 
 void dpo_destroy(dpo_ctx* c) {
   if (!c) return;
-  if (c->kind) hipFree(c->kind);
+  if (c->arrays) hipFree(c->arrays);
   if (c->brick_halo) hipFree(c->brick_halo);
-  if (c->free_node) hipFree(c->free_node);
-  if (c->rinv) hipFree(c->rinv);
-  if (c->gtab) hipFree(c->gtab);
-  if (c->sweep_node) hipFree(c->sweep_node);
-  if (c->sweep_pos) hipFree(c->sweep_pos);
-  if (c->one_cell) hipFree(c->one_cell);
-  if (c->node_tab) hipFree(c->node_tab);
   if (c->tab) hipFree(c->tab);
   if (c->rot) hipFree(c->rot);
   if (c->partial) hipFree(c->partial);
-  if (c->resid) hipFree(c->resid);
   if (c->work) hipFree(c->work);
   if (c->work2) hipFree(c->work2);
   if (c->resid_host) hipHostFree(c->resid_host);
