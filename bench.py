@@ -48,9 +48,9 @@ EVAL_ALGO_BYTES_PER_NODE = 16
 # throttle written (4 + 4 + 1) + the packed foot descriptor written (8).
 GREEDY_BYTES_PER_NODE = 25
 EVALS_PER_GREEDY_NODE = 1 + 64 + 2 + 12
-# VALU wave instructions per wave of 64 nodes of the greedy sweep with foot
-# descriptors, from the SQ_INSTS_VALU counter (profiles/k_sweep_fast_seeded_96x96x96x64.md)
-GREEDY_VALU_PER_WAVE = 2208
+# VALU wave instructions per wave of 64 nodes of the greedy sweep inside a policy-iteration
+# step, from the SQ_INSTS_VALU counter (profiles/k_eval_brick_desc_k_sweep_fast_96x96x96x64.md)
+GREEDY_VALU_PER_WAVE = 1673
 # Gather bytes of one evaluation done naively: 16 float32 corners.
 GATHER_BYTES_PER_EVAL = 64
 

@@ -829,10 +829,11 @@ __device__ inline void search_node(const QF& qf, const Scan& scan, const SweepAr
     S.evals += walk_search(qf, a, a.walk_from[j], qc, ch);
   } else {
     // The full search of a lane that falls back holds up its wave.  Listing
-    // such nodes for a second launch was dearer at every size and rate of
-    // fallbacks: the set-up is formed twice, there in mixed waves, while here it
-    // stands in registers and a one-cell wave's scan is short (64 x 60 x 56 x
-    // 48: 324 us with the second launch, 262 in place; 10 x 27 x 12 x 10: 42 and 20).
+    // such nodes for a second launch was dearer at every size and share of them
+    // measured: the set-up is formed twice, there in mixed waves, while here it
+    // stands in registers and a one-cell wave's scan is short (96^3 x 64, 19 % of
+    // the nodes: 2.40 ms then, 1.33 now, with hardly any 1.38 and 1.02; 64 x 60 x 56
+    // x 48: 0.32 and 0.22; 10 x 27 x 12 x 10: 42 us and 16).
     if (seeded_local(qf, a, a.seed[j], qc, vin, ch)) {
       S.fell_back++;
       scan(bq, bk);
@@ -866,6 +867,9 @@ __device__ inline void fast_node(ConstArgs p, int t, bool live, uint32_t packed,
   NodeTerms T;
   float4 m;
   const int j = node_terms_tab(a, packed, T, m);
+  // the table search evaluates every entry: its window costs more than it saves with 16
+  // angles (32^4: 24.9 us without, 27.5 with) and gains little with 72 (38.4, 38.5;
+  // 96^3 x 64: 1426, 1349)
   constexpr bool kAngles = kOne && (kMode == 1 || kMode == 2);
   WaveAngles W;
   if constexpr (kAngles) load_angles(a, lds, W);
@@ -911,13 +915,12 @@ __device__ inline void fast_node(ConstArgs p, int t, bool live, uint32_t packed,
 // nodes (sweep_node keeps the two kinds apart, see k_order_free) takes the
 // short form, any other the general one.  Vector instruction issue bounds the
 // sweep with many controls (96^3 x 64, coast + scan 64 + golden 12, value
-// iteration: 1.99 -> 1.45 ms a sweep with the two forms, the scan's window and
-// the tables of the node terms; 2212 -> 1570 vector instructions per wave),
-// and the latency of its loads the one with few (40^4, 17 controls: 713 -> 470
-// instructions per wave, 1.2 times as fast).  Splitting the nodes inside
-// the kernel instead (listing the others in LDS, per workgroup or per wave, and
-// running them together) took 1.96-2.8 ms: the second phase leaves lanes and
-// waves idle.
+// iteration: 1.99 -> 1.37 ms a sweep with the two forms, the scan's window and
+// the tables of the node terms; 2007 -> 1458 vector instructions per wave),
+// and the latency of its loads the one with few (40^4, 17 controls: 58 -> 45 us).
+// Splitting the nodes inside the kernel instead (listing the others in LDS, per
+// workgroup or per wave, and running them together) took 1.96-2.8 ms: the second
+// phase leaves lanes and waves idle.
 template <int kMode, bool kBatch>
 __device__ inline void sweep_nodes(ConstArgs p, int tile, float4* lds, bool resid, NodeSums& S) {
   const SweepArgs a = sweep_args<kBatch>(p);
