@@ -29,12 +29,14 @@ constexpr int kOrderChunk = 4096;  // entries of the free list ordered together 
 DPO_HOST_DEVICE inline unsigned long long place_waves(int n, int ones, int chunk, int* slot) {
   const int full = n / 64, pure = ones / 64 < full ? ones / 64 : full, mixed = full - pure;
   const int phase = (chunk * 39) & 63;  // about the golden section of the chunk's number
+  // the m-th mixed wave at (m + phase / 64) full / mixed
+  auto place = [&](int m) { return m < mixed ? (64 * m + phase) * full / (64 * mixed) : full; };
   unsigned long long bits = 0;
-  int p = 0, m = 0;
+  int p = 0, m = 0, next = place(0);
   for (int s = 0; s < full; s++) {
-    // the m-th mixed wave at (m + phase / 64) full / mixed
-    if (m < mixed && (p == pure || s >= (64 * m + phase) * full / (64 * mixed))) {
+    if (s == next) {
       slot[pure + m++] = s;
+      next = place(m);
     } else {
       slot[p++] = s;
       bits |= 1ull << s;
