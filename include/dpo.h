@@ -476,7 +476,8 @@ int dpo_batch_init_value(dpo_batch* b, float* const* V, void* stream);
 
 /* Value iteration of all problems from the given V (in/out, host array of
  * device pointers).  pol_angle / pol_thr: host arrays of device pointers, or
- * NULL; written at the free nodes.  sweeps_per_graph: even, 2..256; block: 64..512 (multiple of 64).
+ * NULL; written at the free nodes, the others' entries stay as they are.
+ * sweeps_per_graph: even, 2..256; block: 64..512 (multiple of 64).
  * stats: host array of n_prob (nullable); *seconds: wall time (nullable).
  * Synchronises `stream` first and runs on the batch's own stream.  Returns
  * DPO_ENOCONV if some problem did not converge within max_sweeps. */
